@@ -21,6 +21,15 @@ int score_rows_per_chunk(int C) {
   return r < 1 ? 1 : r;
 }
 
+// Token rows per workgroup of the score: a whole region (one pass, no finalize launch)
+// when there are enough regions to fill the GPU one workgroup each, or when a region is
+// at most 16 float4 per thread of a 1024-thread workgroup; larger regions are cut.
+int score_rows(const fd_plan* p, int C) {
+  if (p->n_regions >= 2 * fdh::num_cus() || static_cast<long long>(p->max_region_tokens) * C <= 65536)
+    return p->max_region_tokens;
+  return score_rows_per_chunk(C);
+}
+
 struct BlockWs {
   float* mod;
   uint16_t* a;
@@ -231,10 +240,7 @@ fd_status fd_region_score(const fd_plan* plan, int32_t C, const float* x_cur, co
   FD_REQUIRE(x_cur && x_prev && score && ws, "null pointer");
   FD_REQUIRE(aligned(x_cur, 16) && aligned(x_prev, 16) && aligned(ws, 8), "misaligned buffer");
   if (ws_bytes < fd_region_score_ws_size(plan, C)) return fdh::set_error("score workspace too small"), FD_E_SHAPE;
-  // regions cut into chunks of `rows` tokens, unless there are enough regions to
-  // fill the GPU one workgroup each (then one pass, no finalize)
-  int rows = score_rows_per_chunk(C);
-  if (plan->n_regions >= 2 * fdh::num_cus()) rows = plan->max_region_tokens > 0 ? plan->max_region_tokens : 1;
+  const int rows = score_rows(plan, C);
   const int nchunk = (plan->max_region_tokens + rows - 1) / rows;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   FD_LAUNCH(FD_K_SCORE, s,
@@ -292,8 +298,7 @@ fd_status fd_region_score_noalloc(const fd_plan* plan, int32_t C, const float* x
            FD_E_UNSUPPORTED;
   void* ws = nullptr;
   FD_TRY(scratch_address(&ws));
-  int rows = score_rows_per_chunk(C);
-  if (plan->n_regions >= 2 * fdh::num_cus()) rows = plan->max_region_tokens > 0 ? plan->max_region_tokens : 1;
+  const int rows = score_rows(plan, C);
   const int nchunk = (plan->max_region_tokens + rows - 1) / rows;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   FD_LAUNCH(FD_K_SCORE, s,
