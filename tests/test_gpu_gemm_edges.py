@@ -1,0 +1,45 @@
+"""The GEMM variants at the sizes where they change: the embedding with channel counts
+that are and are not a multiple of 64, at the edges of its 128-row tiles."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2607_12121_amd import flashdiff as fdl
+from tests import gpu_harness as gh
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    fdl.lib()
+
+
+@pytest.mark.parametrize("C", [16, 48, 64, 80, 144, 256])
+@pytest.mark.parametrize("M,N,D", [(1, 1, 64), (127, 127, 192), (128, 300, 64), (129, 129, 128), (0, 40, 64), (513, 700, 320)])
+def test_embed_edges(C, M, N, D):
+    """M active rows of N tokens: h = xa w^T + b + pos[idx], rows past M untouched.  The products
+    of bf16 values are exact in fp32, so only the order of C + 2 fp32 additions differs from the
+    float64 result: each row's error is at most (C + 2) 2^-24 of the sum of magnitudes."""
+    gh.say(f"embed C={C} M={M} N={N} D={D}")
+    rng = np.random.default_rng([C, M, N, D])
+    dims = fdl.dims(C, D, D // 64, 64, 64)
+    plan = fdl.make_plan(np.zeros(N, np.int32), np.array([0, N], np.int32), 1)
+    idx = np.sort(rng.permutation(N)[:M]).astype(np.int32)
+    xa = torch.from_numpy(rng.standard_normal((N, C)).astype(np.float32)).to(torch.bfloat16)
+    w = torch.from_numpy(rng.standard_normal((D, C)).astype(np.float32)).to(torch.bfloat16)
+    b = torch.from_numpy(rng.standard_normal(D).astype(np.float32))
+    pos = torch.from_numpy(rng.standard_normal((N, D)).astype(np.float32))
+    h = torch.full((N, D), -7.0, device="cuda")
+    d_idx = torch.zeros(N, dtype=torch.int32, device="cuda")
+    d_idx[:M] = torch.from_numpy(idx).cuda()
+    fdl.fd_embed(plan, dims, xa.cuda(), w.cuda(), b.cuda(), pos.cuda(), d_idx,
+                 torch.tensor([M], dtype=torch.int32, device="cuda"), h)
+    got = h.cpu().double().numpy()
+    x64, w64, p64 = xa.double().numpy()[:M], w.double().numpy(), pos.double().numpy()[idx]
+    want = x64 @ w64.T + b.double().numpy() + p64
+    bound = (C + 2) * 2.0 ** -24 * (np.abs(x64) @ np.abs(w64).T + np.abs(b.double().numpy()) + np.abs(p64))
+    assert np.all(np.abs(got[:M] - want) <= bound)
+    assert np.all(got[M:] == -7.0)
