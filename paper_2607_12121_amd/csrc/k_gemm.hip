@@ -156,7 +156,11 @@ static_assert(kSmallRing >= CfgSmall::STAGES * CfgSmall::CHUNKS + 1 && kSmallRin
 
 constexpr int TBK = 64;
 constexpr int kMaxSplit = 16;
-constexpr int kMinSplitSteps = 24;   // K-steps every split keeps
+// K-steps every split keeps.  16: a split GEMM of 64 tiles and K = 4096 runs on 256 slots instead of
+// 128 (1024 rows x 1024: 30.6 -> 24.7 us with its sum, 256 rows 27.6 -> 19.5; 24 was the line before);
+// from 12 on the QKV and out projections (K = 1024 to 1536) split too, and their sums cost more than
+// the splits give (image out-projection 20.5 -> 26.9 us).
+constexpr int kMinSplitSteps = 16;
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef int int32x4_t __attribute__((ext_vector_type(4)));
@@ -192,7 +196,7 @@ FD_DEVICE void wait_vm_barrier() {
 
 
 // Number of K splits (identical in every WG): split only while every unit keeps
-// at least 24 K-steps and the units still fit the resident workgroup slots.
+// at least kMinSplitSteps K-steps and the units still fit the resident workgroup slots.
 FD_DEVICE int choose_split(int tiles, int nk, int slots, int max_units) {
   int s = 1;
   while (s < kMaxSplit && tiles * (s + 1) <= slots && tiles * (s + 1) <= max_units && nk / (s + 1) >= kMinSplitSteps) ++s;

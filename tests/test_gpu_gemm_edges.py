@@ -1,11 +1,13 @@
 """The GEMM variants at the sizes where they change: the embedding with channel counts
-that are and are not a multiple of 64, at the edges of its 128-row tiles."""
+that are and are not a multiple of 64, at the edges of its 128-row tiles; the down-projection where its split count changes."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2607_12121_amd import flashdiff as fdl
+from paper_2607_12121_amd import workloads as wl
 from tests import gpu_harness as gh
+from tests.helpers import small_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +45,16 @@ def test_embed_edges(C, M, N, D):
     bound = (C + 2) * 2.0 ** -24 * (np.abs(x64) @ np.abs(w64).T + np.abs(b.double().numpy()) + np.abs(p64))
     assert np.all(np.abs(got[:M] - want) <= bound)
     assert np.all(got[M:] == -7.0)
+
+
+@pytest.mark.parametrize("F", [1984, 2048, 3072])
+@pytest.mark.parametrize("tokens,frac", [((40,), 1.0), ((129, 300), 0.5)])
+def test_block_split_edges(F, tokens, frac):
+    """A block whose down-projection has 31 (no split), 32 (two splits) and 48 (three) K-steps."""
+    w = small_workload("audio", requests=tuple(wl.RequestShape("seq", (n,), (16,)) for n in tokens), activity="frac",
+                       activity_args=(frac, 1.0), L=1, D=128, H=2, dh=64, F=F)
+    case = gh.make_case("audio", workload=w)
+    gh.say(f"split edges F={F} tokens={tokens}")
+    g, st = gh.run_gpu(case, case.inp.eps, case.inp.x_cur, case.inp.x_prev)
+    o = gh.run_oracle(case, case.inp.eps, case.inp.x_cur, case.inp.x_prev)
+    gh.compare_step(case, g, o, case.inp.x_cur, st)
