@@ -7,10 +7,15 @@
 // needs no host-side M.
 //
 // Tiled kernel (K % 64 == 0): a BM x BN workgroup tile, BK = 64, WM x WN waves
-// each owning a (BM/WM) x (BN/WN) block of 32x32 MFMA tiles.  Two shapes are
-// built: 128x128 with 4 waves and two workgroups per CU (few active rows), and
-// 256x256 with 8 waves and one workgroup per CU (many rows; half the LDS traffic
-// per flop).  Tiles stream from HBM straight into LDS (buffer_load ... lds, 16
+// each owning a (BM/WM) x (BN/WN) block of 32x32 MFMA tiles.  Two kernels, chosen by the
+// row capacity, each holding several shapes chosen on the device from M: short batches run
+// 256-thread workgroups, two per CU, with 128x64 / 128x128 / 128x192 tiles; long ones
+// 512-thread workgroups, one per CU, with 256x256 (half the LDS traffic per flop, which
+// bounds the K loop: at 256x256 about 2560 LDS clocks beside 2048 MFMA clocks per K-step),
+// 192x256, 128x256, 128x128 or pairs of 128x64 tiles.  With one shape for long batches
+// (256x256) and the small kernel up to 16384 tokens, the audio block's dense warm-up of
+// 13600 rows took 695 us (now 612), the image block at 2048 of 40960 rows 453 (328).
+// Tiles stream from HBM straight into LDS (buffer_load ... lds, 16
 // bytes per lane) through a ring of stages with one barrier per K-step; every
 // stage is issued (the last one re-issued at the tail) so the wait count is a
 // constant.  In LDS each tile row is eight 16-byte chunks, chunk c of row r at
@@ -19,7 +24,7 @@
 // while the current MFMAs run (one read after each of the first MFMAs).  Rows
 // past M (or N) re-read the last valid row; their results are never stored.
 //
-// Split-K (128x128 tiles only, when the tile count leaves CUs idle and K is long):
+// Split-K (128x128 tiles, when the tile count leaves CUs idle and K is long):
 // every tile's K range is cut into S contiguous splits, each storing its fp32 tile
 // to scratch; a second kernel sums the S partials in split order (deterministic)
 // and runs the epilogue.  No workgroup waits for another: the kernel boundary
@@ -118,14 +123,13 @@ FD_DEVICE void epilogue_block(const fdh::GemmArgs& g, bool row_ok, int row, int 
 
 // ---------------------------------------------------------------- tiled kernel
 
-template <int BM_, int BN_, int WM_, int WN_, int STAGES_, int OCC_, int BK_ = 64, bool SPREAD_ = false,
-          int GROUP_M_ = 0>
+template <int BM_, int BN_, int WM_, int WN_, int STAGES_, int GROUPS_ = 1, int GROUP_M_ = 0>
 struct TileCfg {
   static constexpr int GROUP_M = GROUP_M_;   // tile order: groups of GROUP_M row tiles (0: row tile fastest)
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, STAGES = STAGES_, OCC = OCC_, BK = BK_;
-  // SPREAD: the next stage's loads are issued a share per k16 step, between the
-  // MFMAs, instead of all at once after the barrier
-  static constexpr bool SPREAD = SPREAD_;
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, STAGES = STAGES_, BK = 64;
+  // GROUPS = 2: the workgroup's two halves of four waves each run tiles of their own in
+  // their own half of the LDS, sharing only the barriers
+  static constexpr int GROUPS = GROUPS_;
   static constexpr int WAVES = WM * WN, THREADS = WAVES * 64;
   static constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32;
   static constexpr int CPR = BK / 8;                        // 16-byte chunks per tile row
@@ -133,26 +137,37 @@ struct TileCfg {
   static constexpr int CHUNKS = (BM + BN) * CPR;            // 16-byte chunks per stage
   static constexpr int LOADS = (BM + BN) / RPW / WAVES;     // wave-loads per wave per stage
   static constexpr int LOADS_A = BM / RPW / WAVES;          // the first LOADS_A of them fetch A rows
-  static_assert(BK == 64 || BK == 32, "K step of 64 (eight chunks per row) or 32 (four)");
   // chunk c of tile row r sits at c ^ swz(r): the 16 lanes reading one fragment (16
   // consecutive rows, one logical chunk) hit 16 different 16-byte bank groups
-  static FD_DEVICE int swz(int r) { return BK == 64 ? (r >> 1) & 7 : (r >> 2) & 3; }
+  static FD_DEVICE int swz(int r) { return (r >> 1) & 7; }
   static_assert(BM % (RPW * WAVES) == 0 && BN % (RPW * WAVES) == 0, "tile rows must split into whole wave-loads");
   static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be whole 32x32 MFMA blocks");
-  static_assert(STAGES * CHUNKS * 16 <= 160 * 1024, "ring exceeds LDS");
 };
-using CfgSmall = TileCfg<128, 128, 2, 2, 2, 2>;
-using CfgWide = TileCfg<128, 192, 2, 2, 2, 2>;     // 1.5x the columns: one round where 128x128 needs two
+// The 256-thread kernel, two workgroups per CU (short batches).
+using CfgSmall = TileCfg<128, 128, 2, 2, 2>;
+using CfgWide = TileCfg<128, 192, 2, 2, 2>;     // 1.5x the columns: one round where 128x128 needs two
 // half the columns: twice the tiles when few; its 24 KB stages fit three in the
 // shared ring, and the third stage hides the load latency that two exposed
-using CfgNarrow = TileCfg<128, 64, 2, 2, 3, 2>;
-using CfgLarge = TileCfg<256, 256, 2, 4, 2, 1, 64, false, 8>;   // tile order in groups of 8 row tiles
-constexpr int kSmallTile = 128 * 128;   // split-K partial tile (floats)
+using CfgNarrow = TileCfg<128, 64, 2, 2, 3>;
+// The 512-thread kernel, one workgroup per CU.  The three wide ones take their tiles in
+// groups of 8 row tiles; the deep one hides the latency of its short K-steps with a
+// four-stage ring; the pair runs two narrow tiles side by side.
+using CfgLarge = TileCfg<256, 256, 2, 4, 2, 1, 8>;
+using CfgTall = TileCfg<192, 256, 2, 4, 2, 1, 8>;
+using CfgMid = TileCfg<128, 256, 2, 4, 3, 1, 8>;
+using CfgDeep = TileCfg<128, 128, 2, 4, 4>;
+using CfgPair = TileCfg<128, 64, 2, 2, 3, 2>;
+constexpr int kSmallThreads = CfgSmall::THREADS, kLargeThreads = CfgLarge::THREADS;
+static_assert(kSmallThreads == 256 && kLargeThreads == 512 && CfgPair::GROUPS * CfgPair::THREADS == kLargeThreads, "workgroup sizes");
+constexpr int kSmallTile = 128 * 128;   // split-K partial tile (floats): CfgSmall and CfgDeep split
 constexpr int kSideChunks = 4 * 1024 / 16;   // two 1 KB bias slots and two 1 KB token slots (256x256 tile)
-// LDS ring of the two-workgroups-per-CU kernel: the largest of its three tile shapes
-constexpr int kSmallRing = CfgWide::STAGES * CfgWide::CHUNKS;
-static_assert(kSmallRing >= CfgSmall::STAGES * CfgSmall::CHUNKS + 1 && kSmallRing >= CfgNarrow::STAGES * CfgNarrow::CHUNKS,
-              "the small kernel's ring holds every shape (and the split flag past the 128x128 ring)");
+// LDS rings of the two kernels: the shape that needs most
+template <class Cfg> constexpr int ring_chunks() { return Cfg::GROUPS * Cfg::STAGES * Cfg::CHUNKS; }
+constexpr int kSmallRing = ring_chunks<CfgWide>(), kLargeRing = ring_chunks<CfgMid>();
+static_assert(kSmallRing >= ring_chunks<CfgSmall>() && kSmallRing >= ring_chunks<CfgNarrow>(), "the small ring holds every shape");
+static_assert(kLargeRing >= ring_chunks<CfgLarge>() + kSideChunks && kLargeRing >= ring_chunks<CfgTall>() &&
+                  kLargeRing >= ring_chunks<CfgDeep>() && kLargeRing >= ring_chunks<CfgPair>() && kLargeRing * 16 <= 160 * 1024,
+              "the large ring holds every shape (and the side slots past the 256x256 one)");
 
 constexpr int TBK = 64;
 constexpr int kMaxSplit = 16;
@@ -263,9 +278,13 @@ FD_DEVICE void row_operands(const fdh::GemmArgs& g, int M, int row0, int (&rtok)
   }
 }
 
-// All tiles of one GEMM with tile shape Cfg, the workgroup's LDS ring at ring_mem
-// (STAGES * CHUNKS 16-byte chunks, followed by kSideChunks more for the bias and
-// token slots of the 256x256 bf16-output kinds).
+// All tiles of one GEMM with tile shape Cfg, the workgroup's LDS ring at ring_all
+// (STAGES * CHUNKS 16-byte chunks per group, followed by kSideChunks more for the bias
+// and token slots of the 256x256 bf16-output kinds).
+//
+// With two groups, the groups of a workgroup pass the same barriers: a unit has as many
+// as the longest split has K-steps, plus one, and the second group, whose unit comes
+// later in the order, passes them without work when its units have run out.
 //
 // Units follow each other without a drain of the output stores: on the 256x256
 // tile with a bf16 output (QKV, GELU) the next unit's first stage, bias and row
@@ -275,7 +294,7 @@ FD_DEVICE void row_operands(const fdh::GemmArgs& g, int M, int row0, int (&rtok)
 // operations complete in issue order).  That path issues no other vector memory
 // operation the compiler would wait for.
 template <class Cfg, int KIND>
-FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_mem) {
+FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_all) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, FM = Cfg::FM, FN = Cfg::FN, TM = Cfg::TM, TN = Cfg::TN;
   constexpr int WAVES = Cfg::WAVES, THREADS = Cfg::THREADS, LOADS = Cfg::LOADS, STAGES = Cfg::STAGES;
   constexpr bool kOverlap = BM * BN == 256 * 256 && (KIND == fdh::GEMM_QKV || KIND == fdh::GEMM_GELU);
@@ -286,13 +305,16 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
   const int tiles = tiles_m * tiles_n;
   constexpr int BK = Cfg::BK, CPR = Cfg::CPR, RPW = Cfg::RPW;
   const int nk = K / BK;
+  // the 128x128 tiles alone split
   const int S = (BM * BN == kSmallTile && g.max_units > 0) ? choose_split(tiles, nk, slots, g.max_units) : 1;
   const int units = tiles * S;
   const int per_xcd = (units + kXcds - 1) / kXcds;
   constexpr bool overlap = kOverlap;   // g.partial (required) holds the spare slot of skipped stores
   static_assert(!kOverlap || (BN == 256 && BM == 256), "one 16-byte copy per lane covers a slot");
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int group = Cfg::GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / THREADS);
+  const int tid = threadIdx.x - group * THREADS, lane = tid & 63, wave = tid >> 6;
+  uint4* ring_mem = ring_all + group * (STAGES * Cfg::CHUNKS);
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
   const int l32 = lane & 31, lg = lane >> 5;
   const int32x4_t rs_a = buffer_rsrc(g.act);
@@ -300,8 +322,9 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t ring_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)&ring_mem[0]));
 
-  // Work unit u of this workgroup (u = blockIdx.x, + gridDim.x, ...).  gridDim.x is
-  // a multiple of kXcds, so v grows with u and the valid units form a prefix.
+  // Work unit u of this group (u = blockIdx.x + gridDim.x * group, + gridDim.x * GROUPS,
+  // ...).  gridDim.x is a multiple of kXcds, so v grows with u and a workgroup's valid
+  // units form a prefix.
   struct Unit { int v, split, m0, n0, kt0, nkt; };
   auto unit_at = [&](int u, Unit& t) -> bool {
     if (u >= per_xcd * kXcds) return false;
@@ -381,9 +404,17 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
                                 : make_float4(0.f, 0.f, 0.f, 0.f);
   };
 
+  const int barriers = (nk + S - 1) / S + 1;   // of every unit
+  auto pass_barriers = [&](int n) {
+    for (int i = 0; i < n; ++i) __builtin_amdgcn_s_barrier();
+  };
   Unit cur;
-  int u = blockIdx.x;
-  if (!unit_at(u, cur)) return;
+  int u = blockIdx.x + gridDim.x * group;
+  if (!unit_at(u, cur)) {
+    Unit other;
+    if (group > 0 && unit_at(u - gridDim.x, other)) pass_barriers(barriers);   // beside the first group's last unit
+    return;
+  }
   uint32_t off[LOADS];
   offsets(cur, off);
   // this lane's output rows (one per 32-row block) and their token / request,
@@ -418,7 +449,7 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
         wait_vm_barrier<(STAGES - 2) * LOADS>();
       // refill the slot every wave finished reading before this barrier (a repeat at the tail)
       const int kt_next = min(it + STAGES - 1, nkt - 1), st_next = (it + STAGES - 1) % STAGES;
-      if constexpr (!Cfg::SPREAD) issue_q(off, kt0, kt_next, st_next, 0, LOADS);
+      issue_q(off, kt0, kt_next, st_next, 0, LOADS);
       const uint4* sm = ring_mem + (it % STAGES) * Cfg::CHUNKS;
       bf16x8_t a[2][FM], b[2][FN];
       auto frag = [&](int ks, int slot) {
@@ -438,10 +469,6 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
 #pragma unroll
       for (int ks = 0; ks < BK / 16; ++ks) {
         if (ks + 1 < BK / 16) frag(ks + 1, (ks + 1) & 1);
-        if constexpr (Cfg::SPREAD) {
-          constexpr int LQ = (LOADS + BK / 16 - 1) / (BK / 16);
-          issue_q(off, kt0, kt_next, st_next, ks * LQ, (ks + 1) * LQ);
-        }
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -464,11 +491,12 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
     }
     // the tail re-issue may still be landing: drain it before the ring is reused
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (Cfg::GROUPS > 1) pass_barriers(barriers - 1 - nkt);   // a split one K-step shorter than the longest
     __syncthreads();
 
     const int row0 = cur.m0 + wm * TM + l32, cw = cur.n0 + wn * TN;
     Unit nxt;
-    u += gridDim.x;
+    u += gridDim.x * Cfg::GROUPS;
     const bool more = unit_at(u, nxt);
     if (S > 1) {
       // Store this split's fp32 tile for splitk_reduce_kernel (float4 r4 of block
@@ -510,7 +538,10 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
     } else {
       tile_epilogue<FM, FN, KIND>(g, M, row0, cw, lg, rtok, rreq, acc);
     }
-    if (!more) return;
+    if (!more) {
+      if (group > 0 && unit_at(u - gridDim.x, nxt)) pass_barriers(barriers);   // beside the first group's last unit
+      return;
+    }
     cur = nxt;
     offsets(cur, off);
     if constexpr (!overlap) row_operands<FM, KIND>(g, M, cur.m0 + wm * TM + l32, rtok, rreq);
@@ -539,7 +570,7 @@ FD_DEVICE int small_shape(int M, int N, int K, int slots, int max_units) {
 }
 
 template <int KIND>
-__global__ __launch_bounds__(256, 2) void gemm_small_kernel(fdh::GemmArgs g, int slots) {
+__global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(fdh::GemmArgs g, int slots) {
   __shared__ uint4 ring_mem[kSmallRing];
   const int M = min(*g.m, g.n_max);
   if (M <= 0) return;
@@ -550,12 +581,46 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(fdh::GemmArgs g, int
   }
 }
 
+// Tile shape of the 512-thread kernel for M rows (identical in every workgroup): 128x128
+// with split-K wherever that applies; otherwise the shape whose rounds of tiles over the
+// CUs cost least.  A round's cost is its time per K-step in 50 ns, measured at 970 to 13824
+// rows x 1536 to 6144 columns: 256x256 27, 192x256 22, 128x256 16, 128x128 10; two 128x64
+// tiles per CU 10, one 7.  Ties go to the larger tile.
+enum LargeShape { kLargeTile = 0, kTallTile = 1, kMidTile = 2, kDeepTile = 3, kPairTile = 4 };
+FD_DEVICE int large_shape(int M, int N, int K, int cus, int max_units) {
+  auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  // rounds of t tiles: a multiply (five integer divisions cost every launch half a microsecond);
+  // t is far below 2^23 and the slack far above the product's error, far below 1 / cus
+  const float inv = 1.0f / static_cast<float>(cus);
+  auto rounds = [&](int t) { return static_cast<int>(ceilf(static_cast<float>(t) * inv - 1e-4f)); };
+  const int t128 = tiles(128, 128), r64 = rounds(tiles(128, 64));
+  if (max_units > 0 && choose_split(t128, K / TBK, cus, max_units) > 1) return kDeepTile;
+  int best = kLargeTile, cost = 27 * rounds(tiles(256, 256));
+  auto consider = [&](int shape, int c) {
+    if (c < cost) {
+      best = shape;
+      cost = c;
+    }
+  };
+  consider(kTallTile, 22 * rounds(tiles(192, 256)));
+  consider(kMidTile, 16 * rounds(tiles(128, 256)));
+  consider(kDeepTile, 10 * rounds(t128));
+  consider(kPairTile, (r64 >> 1) * 10 + (r64 & 1) * 7);
+  return best;
+}
+
 template <int KIND>
-__global__ __launch_bounds__(CfgLarge::THREADS, CfgLarge::OCC) void gemm_large_kernel(fdh::GemmArgs g, int slots) {
-  __shared__ uint4 ring_mem[CfgLarge::STAGES * CfgLarge::CHUNKS + kSideChunks];   // ring + bias and token slots
+__global__ __launch_bounds__(kLargeThreads, 2) void gemm_large_kernel(fdh::GemmArgs g, int cus) {
+  __shared__ uint4 ring_mem[kLargeRing];
   const int M = min(*g.m, g.n_max);
   if (M <= 0) return;
-  gemm_tiles<CfgLarge, KIND>(g, slots, M, ring_mem);
+  switch (large_shape(M, g.N, g.K, cus, g.max_units)) {
+    case kLargeTile: gemm_tiles<CfgLarge, KIND>(g, cus, M, ring_mem); break;
+    case kTallTile: gemm_tiles<CfgTall, KIND>(g, cus, M, ring_mem); break;
+    case kMidTile: gemm_tiles<CfgMid, KIND>(g, cus, M, ring_mem); break;
+    case kDeepTile: gemm_tiles<CfgDeep, KIND>(g, cus, M, ring_mem); break;
+    default: gemm_tiles<CfgPair, KIND>(g, 2 * cus, M, ring_mem); break;
+  }
 }
 
 // Split-K reduction: when the GEMM above split its 128x128 tiles (same M, shape and
@@ -564,9 +629,8 @@ __global__ __launch_bounds__(CfgLarge::THREADS, CfgLarge::OCC) void gemm_large_k
 // workgroup per (tile, 32x32 block of every wave): four per tile, so that each
 // thread keeps all of its S partial loads in flight.  The kernel boundary orders
 // the partial stores before these loads.
-template <int KIND>
-__global__ __launch_bounds__(CfgSmall::THREADS) void splitk_reduce_kernel(fdh::GemmArgs g, int slots) {
-  using Cfg = CfgSmall;
+template <int KIND, class Cfg>
+__global__ __launch_bounds__(Cfg::THREADS) void splitk_reduce_kernel(fdh::GemmArgs g, int slots) {
   constexpr int FM = Cfg::FM, FN = Cfg::FN, NB = FM * FN, THREADS = Cfg::THREADS;
   const int M = min(*g.m, g.n_max);
   if (M <= 0) return;
@@ -727,34 +791,44 @@ size_t gemm_scratch_bytes() {
 }
 
 namespace {
-// Row capacity (token count of the batch) from which the 256x256 tile is used.
-// The active row count is only known on the device, so the choice rests on the
-// capacity: at the active fractions the gate produces (20-70%), 16384 tokens give
-// thousands of active rows, enough for one 256x256 tile per CU at N >= 1536.
-constexpr int kLargeTileRows = 16384;
+// Row capacity (token count of the batch) from which the 512-thread kernel is used.  The
+// active row count is only known on the device, so the choice rests on the capacity; its
+// shapes hold for few rows too.  13824 tokens of 6 requests, image dims, us per block, small
+// / large kernel: 7% active 179 / 179, 22% 378 / 355, 30% 488 / 440, 70% 1012 / 860; below
+// 8192 tokens (1664 of 4096 rows: 221 / 224) the two small workgroups per CU win.
+constexpr int kLargeTileRows = 8192;
+// Row capacity from which no GEMM splits: a split needs at most 128 tiles of 128x128, under
+// 5% of the rows here, and the sum's launch, empty otherwise, costs every call 4 us.
+constexpr int kNoSplitRows = 16384;
 
-// Persistent grid: at most the resident slots, at least one workgroup per unit
-// the largest unit count could need (narrowest tile, every split).
+// Persistent grid: at most the resident workgroups, at least one per unit the largest
+// unit count could need (narrowest tile, every split).
 hipError_t launch_tiled(GemmKind kind, const GemmArgs& a, int max_units, bool large, hipStream_t s) {
-  const int occ = large ? CfgLarge::OCC : 2;
-  const int slots = num_cus() * occ;
+  const int slots = num_cus() * (large ? 1 : 2);
   GemmArgs g = a;
   g.max_units = max_units;
-  const int bm = large ? CfgLarge::BM : 128, bn = large ? CfgLarge::BN : CfgNarrow::BN;
-  const long long tiles_max = static_cast<long long>((a.n_max + bm - 1) / bm) * ((a.N + bn - 1) / bn);
+  const long long tiles_max =
+      static_cast<long long>((a.n_max + CfgNarrow::BM - 1) / CfgNarrow::BM) * ((a.N + CfgNarrow::BN - 1) / CfgNarrow::BN);
   long long grid = tiles_max * (max_units > 0 ? kMaxSplit : 1);
   if (grid > slots) grid = slots;
   grid = ((grid + kXcds - 1) / kXcds) * kXcds;
 #define FD_GEMM_LAUNCH(K)                                                                      \
   if (large)                                                                                   \
-    gemm_large_kernel<K><<<grid, CfgLarge::THREADS, 0, s>>>(g, slots);                         \
+    gemm_large_kernel<K><<<grid, kLargeThreads, 0, s>>>(g, slots);                             \
   else                                                                                         \
-    gemm_small_kernel<K><<<grid, 256, 0, s>>>(g, slots);
+    gemm_small_kernel<K><<<grid, kSmallThreads, 0, s>>>(g, slots);
+#define FD_REDUCE_LAUNCH(K)                                                                    \
+  if (large)                                                                                   \
+    splitk_reduce_kernel<K, CfgDeep><<<red_grid, CfgDeep::THREADS, 0, s>>>(g, slots);          \
+  else                                                                                         \
+    splitk_reduce_kernel<K, CfgSmall><<<red_grid, CfgSmall::THREADS, 0, s>>>(g, slots);
   // the split-K reduction, launched whenever K is long enough for a split (it
   // returns at once when the device-side M gave S = 1)
-  const bool may_split = !large && max_units > 0 && (a.K / TBK) >= 2 * kMinSplitSteps;
-  const long long red_units = static_cast<long long>((a.n_max + 127) / 128) * ((a.N + 127) / 128) * CfgSmall::FM * CfgSmall::FN;
-  const int red_grid = static_cast<int>(red_units < 4 * slots ? red_units : 4 * slots);
+  const bool may_split = max_units > 0 && (a.K / TBK) >= 2 * kMinSplitSteps;
+  // at most slots / 2 tiles split, one workgroup per 32x32 block of every wave's tile
+  const long long red_units = static_cast<long long>((a.n_max + 127) / 128) * ((a.N + 127) / 128);
+  const int red_grid = static_cast<int>(red_units < slots / 2 ? red_units : slots / 2) *
+                       (large ? CfgDeep::FM * CfgDeep::FN : CfgSmall::FM * CfgSmall::FN);
   switch (kind) {
     case GEMM_QKV: FD_GEMM_LAUNCH(GEMM_QKV) break;
     case GEMM_RESID: FD_GEMM_LAUNCH(GEMM_RESID) break;
@@ -762,29 +836,31 @@ hipError_t launch_tiled(GemmKind kind, const GemmArgs& a, int max_units, bool la
     case GEMM_EMBED: FD_GEMM_LAUNCH(GEMM_EMBED) break;
     case GEMM_OUT: FD_GEMM_LAUNCH(GEMM_OUT) break;
   }
-#undef FD_GEMM_LAUNCH
   if (may_split) {
     switch (kind) {
-      case GEMM_QKV: splitk_reduce_kernel<GEMM_QKV><<<red_grid, CfgSmall::THREADS, 0, s>>>(g, slots); break;
-      case GEMM_RESID: splitk_reduce_kernel<GEMM_RESID><<<red_grid, CfgSmall::THREADS, 0, s>>>(g, slots); break;
-      case GEMM_GELU: splitk_reduce_kernel<GEMM_GELU><<<red_grid, CfgSmall::THREADS, 0, s>>>(g, slots); break;
-      case GEMM_EMBED: splitk_reduce_kernel<GEMM_EMBED><<<red_grid, CfgSmall::THREADS, 0, s>>>(g, slots); break;
-      case GEMM_OUT: splitk_reduce_kernel<GEMM_OUT><<<red_grid, CfgSmall::THREADS, 0, s>>>(g, slots); break;
+      case GEMM_QKV: FD_REDUCE_LAUNCH(GEMM_QKV) break;
+      case GEMM_RESID: FD_REDUCE_LAUNCH(GEMM_RESID) break;
+      case GEMM_GELU: FD_REDUCE_LAUNCH(GEMM_GELU) break;
+      case GEMM_EMBED: FD_REDUCE_LAUNCH(GEMM_EMBED) break;
+      case GEMM_OUT: FD_REDUCE_LAUNCH(GEMM_OUT) break;
     }
   }
+#undef FD_GEMM_LAUNCH
+#undef FD_REDUCE_LAUNCH
   return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_gemm(GemmKind kind, const GemmArgs& a, hipStream_t s) {
   if (a.K % TBK == 0) {
-    const int max_units = a.partial ? a.max_units : 0;   // no scratch: never split
-    if (a.n_max >= kLargeTileRows && a.N >= 1024) {
-      // the bf16-output kinds send the stores of rows past M to a spare slot in the scratch
-      if ((kind == GEMM_QKV || kind == GEMM_GELU) && !a.partial) return hipErrorInvalidValue;
-      return launch_tiled(kind, a, 0, true, s);
-    }
-    return launch_tiled(kind, a, max_units, false, s);
+    int max_units = a.partial ? a.max_units : 0;   // no scratch: never split
+    // the embedding, whose K-steps are few, is bound by its epilogue, which more and smaller
+    // workgroups run as well (9676 x 1536: 42 / 39 us small / large kernel, 13600 x 1024: 41 / 45)
+    const bool large = a.n_max >= (kind == GEMM_EMBED ? kNoSplitRows : kLargeTileRows) && a.N >= 1024;
+    // its bf16-output kinds send the stores of rows past M to a spare slot in the scratch
+    if (large && (kind == GEMM_QKV || kind == GEMM_GELU) && !a.partial) return hipErrorInvalidValue;
+    if (a.n_max >= kNoSplitRows) max_units = 0;
+    return launch_tiled(kind, a, max_units, large, s);
   }
   if (kind != GEMM_EMBED) return hipErrorInvalidValue;   // D and F are multiples of 64, only C is not
   const long long tiles = static_cast<long long>((a.n_max + BM - 1) / BM) * ((a.N + BN - 1) / BN);
