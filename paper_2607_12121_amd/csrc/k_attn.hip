@@ -28,12 +28,13 @@
 // Schedule: the key tiles of all (head, query tile) items, head-major, form one
 // range cut into equal contiguous shares, one per workgroup of the persistent grid;
 // a share that ends inside an item leaves a piece of it to the next share.  Each
-// piece of a cut item stores its O divided by its own sum (bf16), its max and its
-// sum (fp32), and a second kernel merges the pieces in key order, each weighted by
+// piece of a cut item stores its O divided by its own sum, its max and its
+// sum, and a second kernel merges the pieces in key order, each weighted by
 // 2^(max - overall max) * sum (deterministic for a given grid); no workgroup
 // waits for another.  Shares are dealt to the 8 XCDs in contiguous chunks so that
-// the query tiles sharing a head's K/V run on the same L2.  Head dim 128 and
-// launches without scratch for a partial per piece use runs of whole items.
+// the query tiles sharing a head's K/V run on the same L2.  Where a cut would not
+// shorten the longest share by more than it costs, and without scratch for a partial
+// per piece, shares are runs of whole items.
 #include <type_traits>
 
 #include "fd_common.h"
@@ -227,6 +228,23 @@ FD_DEVICE long long uniform(long long v) {
   return static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
+// floor(q / d) for 0 <= q < 2^50, d >= 1, as a double multiply by the refined reciprocal
+// and one correction (a 64-bit integer division takes about 0.4 us of dependent code, and a
+// workgroup's first piece needed eight: 3.2 to 4.5 us of the image pass's 60)
+FD_DEVICE double reciprocal(long long d) {
+  const double x = static_cast<double>(d);
+  double r = __builtin_amdgcn_rcp(x);   // 1 ulp of single precision or better: two Newton steps
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+FD_DEVICE long long div_by(long long q, long long d, double inv) {
+  long long r = static_cast<long long>(static_cast<double>(q) * inv);
+  const long long rem = q - r * d;
+  r += rem >= d ? 1 : 0;
+  r -= rem < 0 ? 1 : 0;
+  return r;
+}
+
 // Schedule: the key tiles of every item, items head-major, form one range of
 // `work` tile-steps cut into G contiguous shares, one per workgroup, numbered so
 // that each XCD gets consecutive shares (the query tiles of a head share its K/V
@@ -239,19 +257,29 @@ FD_DEVICE long long uniform(long long v) {
 // there is no continuation and slot 2w stays unused).  Without cuts every share
 // boundary is rounded up to the next item start.  Requests are found by binary
 // search in the workgroup's prefix tables.
+// What a cut costs, in tile-steps (1.3 us at head dim 64, 1.8 at 128): the extra pieces'
+// queries, first tiles and stores, and the merge.  Measured, us per attention, whole / cut:
+// head dim 128, 60 items of 64 key tiles 108 / 65, 24 of 16 36 / 31, 192 of 16 47 / 61, 144
+// of 2 15 / 31; head dim 64, 12 of 16 26 / 20, 16 of 8 19 / 18, 16 of 4 15 / 17.
+constexpr int kCutCost = 7;
+constexpr int kMinShareSteps = 4;   // 2, 3, 4 and 6 measured: 24 / 24 / 21 / 26 us for 48 items of 16
+
 template <int QB, bool TABLES>
 struct AttnSched {
   const SchedTables* t;         // TABLES: the workgroup's prefix tables
   const int32_t* cu_q;          // else the requests are walked
   const int32_t* req_tok_off;
-  int B, G;
+  int B, G;               // G: shares, a multiple of the XCDs when they cut
   int tiles;              // query tiles over all requests
   long long work_head;    // tile-steps of one head (key tiles summed over every query tile)
   long long work;         // ... of every head
+  long long per;          // share x starts at x * per + min(x, extra)
+  int extra;
   bool cut;
+  bool narrow;            // work for the whole grid (head dim <= 64: pieces then store O in bf16)
 
   FD_DEVICE AttnSched(const SchedTables* tab, const int32_t* cq, const int32_t* rto, int B_, int H, int G_,
-                      int max_units)
+                      int max_units, int nkv_max)
       : t(tab), cu_q(cq), req_tok_off(rto), B(B_), G(G_), tiles(0), work_head(0) {
     if constexpr (TABLES) {
       tiles = uniform(t->tpre[B]);
@@ -264,16 +292,33 @@ struct AttnSched {
       }
     }
     work = work_head * H;
-    // Shares may cut items when the scratch holds two partials per share and
-    // every share gets a tile-step; otherwise every share is a run of whole items.
-    cut = max_units >= 2 * G && work >= static_cast<long long>(G) && G % kXcds == 0;
+    // Shares cut items when the scratch holds two partials per share and the longest share
+    // gets shorter by more than the pieces' fixed cost; otherwise every share is a run of
+    // whole items: one of the longest at most while there are items for every workgroup no
+    // more than once, else up to one more than its part.  Little work runs on as many
+    // workgroups as give each kMinShareSteps tile-steps.
+    const long long part = div_by(work, G, reciprocal(G));
+    const long long whole = static_cast<long long>(tiles) * H <= G ? nkv_max : part + nkv_max;
+    cut = max_units >= 2 * G && G % kXcds == 0 && (part > kMinShareSteps ? part : kMinShareSteps) + kCutCost < whole;
+    narrow = work >= G;
+    if (cut) {
+      const long long want = div_by(work + kMinShareSteps - 1, kMinShareSteps, 1.0 / kMinShareSteps);
+      const long long up = (want + kXcds - 1) / kXcds * kXcds;
+      if (up < G) G = static_cast<int>(up);
+    }
+    per = div_by(work, G, reciprocal(G));
+    extra = static_cast<int>(work - per * G);
   }
-  // the share run by workgroup `blk`
-  FD_DEVICE int share(int blk) const { return (G % kXcds == 0) ? (blk % kXcds) * (G / kXcds) + blk / kXcds : blk; }
+  // the share run by workgroup `blk` (G: none)
+  FD_DEVICE int share(int blk) const {
+    const int per_xcd = G / kXcds;
+    if (G % kXcds != 0) return blk;
+    return blk / kXcds < per_xcd ? (blk % kXcds) * per_xcd + blk / kXcds : G;
+  }
   // tile-step q < work: its item's first tile-step and key tiles, head, request,
   // the request's first query tile and the query tile
   FD_DEVICE void locate(long long q, long long& i_start, int& nkv, int& head, int& b, int& first, int& tau) const {
-    head = static_cast<int>(q / work_head);
+    head = static_cast<int>(div_by(q, work_head, reciprocal(work_head)));
     long long r = q - static_cast<long long>(head) * work_head;
     if constexpr (!TABLES) {   // few requests: walk them (requests without tile-steps are passed over)
       b = 0;
@@ -287,8 +332,9 @@ struct AttnSched {
         r -= span;
         first += nt;
       }
-      tau = first + static_cast<int>(r / nkv);
-      i_start = q - r % nkv;
+      const long long t = div_by(r, nkv, reciprocal(nkv));
+      tau = first + static_cast<int>(t);
+      i_start = q - (r - t * nkv);
       return;
     }
     // the request: the largest b < B with wpre[b] <= r, which has tile-steps
@@ -302,23 +348,25 @@ struct AttnSched {
     first = uniform(t->tpre[b]);
     const int nt = uniform(t->tpre[b + 1]) - first;
     const long long w0 = uniform(t->wpre[b]);
-    nkv = static_cast<int>((uniform(t->wpre[b + 1]) - w0) / nt);
+    nkv = static_cast<int>(div_by(uniform(t->wpre[b + 1]) - w0, nt, reciprocal(nt)));
     r -= w0;
-    tau = first + static_cast<int>(r / nkv);
-    i_start = q - r % nkv;
+    const long long y = div_by(r, nkv, reciprocal(nkv));
+    tau = first + static_cast<int>(y);
+    i_start = q - (r - y * nkv);
   }
   FD_DEVICE long long bound(long long x) const {   // first tile-step of share x (x <= G)
-    const long long q = x * work / G;
+    if (x >= G) return work;
+    const long long q = x * per + (x < extra ? x : extra);
     if (cut || q >= work) return q;
     long long i_start;
     int nkv, head, b, first, tau;
     locate(q, i_start, nkv, head, b, first, tau);
     return i_start == q ? q : i_start + nkv;
   }
-  FD_DEVICE int share_of(long long q) const {   // the share holding tile-step q
-    int x = static_cast<int>(q * G / work);
-    while (x + 1 < G && bound(x + 1) <= q) ++x;
-    return x;
+  FD_DEVICE int share_of(long long q) const {   // the share holding tile-step q (cut schedules: per >= 1)
+    const long long long_end = extra * (per + 1);   // the first `extra` shares hold one tile-step more
+    if (q < long_end) return static_cast<int>(div_by(q, per + 1, reciprocal(per + 1)));
+    return extra + static_cast<int>(div_by(q - long_end, per, reciprocal(per)));
   }
   // scratch slot of piece j of a cut item whose first piece is in share f
   FD_DEVICE static int slot_of(int f, int j) { return j == 0 ? 2 * f + 1 : 2 * (f + j); }
@@ -351,14 +399,15 @@ template <int DH>
 __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_eu(ACfg<DH>::WPE, ACfg<DH>::WPE))) void attn_fwd_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
     uint16_t* __restrict__ O, int D, int H, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ req_tok_off,
-    int B, float scale_log2, float* __restrict__ partial, int max_units, float* __restrict__ lse) {
+    int B, float scale_log2, float* __restrict__ partial, int max_units, int nkv_max, float* __restrict__ lse) {
   using C = ACfg<DH>;
   constexpr int DT = C::DT, KS = C::KS, KCH = C::KCH, STAGES = C::STAGES, LOADS = C::LOADS, QG = C::QG, QB = C::QB;
   __shared__ uint4 ring[STAGES][C::STAGE];
   __shared__ SchedTables tabs;
 
   build_sched_tables<C::THREADS>(tabs, cu_q, req_tok_off, B, QB);
-  const AttnSched<QB, true> sch(&tabs, cu_q, req_tok_off, B, H, static_cast<int>(gridDim.x), max_units);
+  const AttnSched<QB, true> sch(&tabs, cu_q, req_tok_off, B, H, static_cast<int>(gridDim.x), max_units,
+                                nkv_max);
   if (sch.tiles == 0) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -803,11 +852,11 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
     for (int g = 0; g < QG; ++g) l_run[g] = half_sum(l_run[g]);
 
     if (npieces > 1) {
-      // a piece of a cut item: O / sum rounded to bf16 (a convex combination of V
-      // rows, so bf16 keeps its range) and (max, sum) in fp32 for
-      // attn_combine_kernel, lane-major (the four bf16 of quad q of thread t at
-      // 8-byte word q * THREADS + t, then, past the slot's O area, the (max, sum)
-      // pair of group g at float2 g * THREADS + t)
+      // a piece of a cut item: O / sum and, for attn_combine_kernel, (max, sum) in fp32,
+      // lane-major (quad q of thread t at word q * THREADS + t, then, past the slot's O
+      // area, the (max, sum) pair of group g at float2 g * THREADS + t).  The quads are
+      // fp32; where many pieces make their traffic count (head dim <= 64, work for the
+      // whole grid: image 3 us) bf16, which a convex combination of V rows never leaves.
       constexpr int E = QG * (DT * 16 + 2);
       float* slot = partial + static_cast<size_t>(AttnSched<QB, true>::slot_of(share0, piece)) * (E * C::THREADS);
       uint2* quads = reinterpret_cast<uint2*>(slot) + tid;
@@ -818,10 +867,15 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int d = 0; d < DT; ++d)
 #pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4)
-            quads[((g * DT + d) * 4 + r4) * C::THREADS] =
-                make_uint2(fd::pack_bf2(oacc[g][d][4 * r4] * inv, oacc[g][d][4 * r4 + 1] * inv),
-                           fd::pack_bf2(oacc[g][d][4 * r4 + 2] * inv, oacc[g][d][4 * r4 + 3] * inv));
+          for (int r4 = 0; r4 < 4; ++r4) {
+            const float4 o = make_float4(oacc[g][d][4 * r4] * inv, oacc[g][d][4 * r4 + 1] * inv,
+                                         oacc[g][d][4 * r4 + 2] * inv, oacc[g][d][4 * r4 + 3] * inv);
+            const int at = ((g * DT + d) * 4 + r4) * C::THREADS;
+            if (DH < 128 && sch.narrow)
+              quads[at] = make_uint2(fd::pack_bf2(o.x, o.y), fd::pack_bf2(o.z, o.w));
+            else
+              (reinterpret_cast<float4*>(slot) + tid)[at] = o;
+          }
         ml[g * C::THREADS] = fd::f32x2_t{m_run[g], l_run[g]};
       }
       return;
@@ -861,10 +915,11 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
 template <int DH, bool TABLES>
 FD_DEVICE void combine_items(uint16_t* __restrict__ O, int D, int H, const int32_t* __restrict__ cu_q,
                              const int32_t* __restrict__ req_tok_off, int B, const float* __restrict__ partial,
-                             int max_units, float* __restrict__ lse, const SchedTables* tabs) {
+                             int max_units, int nkv_max, float* __restrict__ lse, const SchedTables* tabs) {
   using C = ACfg<DH>;
   constexpr int DT = C::DT, QG = C::QG, QB = C::QB, E = QG * (DT * 16 + 2);
-  const AttnSched<QB, TABLES> sch(tabs, cu_q, req_tok_off, B, H, static_cast<int>(gridDim.x), max_units);
+  const AttnSched<QB, TABLES> sch(tabs, cu_q, req_tok_off, B, H, static_cast<int>(gridDim.x), max_units,
+                                nkv_max);
   if (sch.tiles == 0 || !sch.cut) return;
   const int x = sch.share(static_cast<int>(blockIdx.x));
   const long long p0 = sch.bound(x), p_end = sch.bound(x + 1);
@@ -901,33 +956,48 @@ FD_DEVICE void combine_items(uint16_t* __restrict__ O, int D, int H, const int32
     for (int d = 0; d < DT; ++d)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[d][r] = 0.f;
-    for (int j0 = 0; j0 < npieces; j0 += 2) {
-      uint2 pv[2][DT * 4];
-      fd::f32x2_t mls[2];
+    auto merge = [&](auto quad_tag) {
+      using Quad = decltype(quad_tag);   // uint2: bf16 pieces, float4: fp32 pieces
+      for (int j0 = 0; j0 < npieces; j0 += 2) {
+        Quad pv[2][DT * 4];
+        fd::f32x2_t mls[2];
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const bool has = j0 + k < npieces;
-        const uint2* quads = reinterpret_cast<const uint2*>(slot(has ? j0 + k : j0)) + tid;
+        for (int k = 0; k < 2; ++k) {
+          const bool has = j0 + k < npieces;
+          const Quad* quads = reinterpret_cast<const Quad*>(slot(has ? j0 + k : j0)) + tid;
 #pragma unroll
-        for (int q = 0; q < DT * 4; ++q) pv[k][q] = quads[(g * DT * 4 + q) * C::THREADS];
-        mls[k] = has ? ml_of(j0 + k, g) : fd::f32x2_t{-INFINITY, 0.f};
+          for (int q = 0; q < DT * 4; ++q) pv[k][q] = quads[(g * DT * 4 + q) * C::THREADS];
+          mls[k] = has ? ml_of(j0 + k, g) : fd::f32x2_t{-INFINITY, 0.f};
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          // the piece's O is normalised by its own sum: weight exp2(m_k - m) * l_k
+          const float wl = (mls[k][0] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mls[k][0] - m_all) * mls[k][1];
+          l_all += wl;
+#pragma unroll
+          for (int d = 0; d < DT; ++d)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+              const Quad w = pv[k][d * 4 + r4];
+              float o[4];
+              if constexpr (sizeof(Quad) == 8) {
+                o[0] = __uint_as_float(w.x << 16);
+                o[1] = __uint_as_float(w.x & 0xffff0000u);
+                o[2] = __uint_as_float(w.y << 16);
+                o[3] = __uint_as_float(w.y & 0xffff0000u);
+              } else {
+                o[0] = w.x; o[1] = w.y; o[2] = w.z; o[3] = w.w;
+              }
+#pragma unroll
+              for (int e = 0; e < 4; ++e) oacc[d][4 * r4 + e] += wl * o[e];
+            }
+        }
       }
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        // the piece's O is normalised by its own sum: weight exp2(m_k - m) * l_k
-        const float wl = (mls[k][0] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mls[k][0] - m_all) * mls[k][1];
-        l_all += wl;
-#pragma unroll
-        for (int d = 0; d < DT; ++d)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const uint2 w2 = pv[k][d * 4 + r / 4];
-            const uint32_t wd = (r % 4) < 2 ? w2.x : w2.y;
-            const float o = (r % 2) == 0 ? __uint_as_float(wd << 16) : __uint_as_float(wd & 0xffff0000u);
-            oacc[d][r] += wl * o;
-          }
-      }
-    }
+    };
+    if (DH < 128 && sch.narrow)
+      merge(uint2{});
+    else
+      merge(float4{});
     if (qrow < q_hi) store_o<DH>(O, lse, D, H, head, qrow, lg, oacc, m_all, l_all);
   }
 }
@@ -937,13 +1007,13 @@ FD_DEVICE void combine_items(uint16_t* __restrict__ O, int D, int H, const int32
 template <int DH, bool TABLES>
 __global__ __launch_bounds__(ACfg<DH>::THREADS) void attn_combine_kernel(
     uint16_t* __restrict__ O, int D, int H, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ req_tok_off,
-    int B, const float* __restrict__ partial, int max_units, float* __restrict__ lse) {
+    int B, const float* __restrict__ partial, int max_units, int nkv_max, float* __restrict__ lse) {
   if constexpr (TABLES) {
     __shared__ SchedTables tabs;
     build_sched_tables<ACfg<DH>::THREADS>(tabs, cu_q, req_tok_off, B, ACfg<DH>::QB);
-    combine_items<DH, true>(O, D, H, cu_q, req_tok_off, B, partial, max_units, lse, &tabs);
+    combine_items<DH, true>(O, D, H, cu_q, req_tok_off, B, partial, max_units, nkv_max, lse, &tabs);
   } else {
-    combine_items<DH, false>(O, D, H, cu_q, req_tok_off, B, partial, max_units, lse, nullptr);
+    combine_items<DH, false>(O, D, H, cu_q, req_tok_off, B, partial, max_units, nkv_max, lse, nullptr);
   }
 }
 
@@ -964,29 +1034,31 @@ hipError_t launch_attention(const uint16_t* q, const uint16_t* kc, const uint16_
   if (B < 1 || B > kMaxSchedRequests) return hipErrorInvalidValue;   // the schedule tables' size
   const int occ = dh >= 128 ? ACfg<128>::OCC : ACfg<64>::OCC;
   const int slots = occ * num_cus();
-  // head dim 128: every workgroup runs whole (head, query tile) items (cut items
-  // measured no faster: the kernel runs at the power limit); smaller heads cut items
-  // into pieces that attn_combine_kernel merges
-  const int max_units = (partial && dh < 128) ? gemm_max_tiles() : 0;
   // persistent grid: the resident slots, fewer when even one key tile per share
   // would leave some idle (upper bound on the items: every request adds at most
   // one partial query tile)
   const int qb = dh >= 128 ? ACfg<128>::QB : ACfg<64>::QB;
   const long long items = static_cast<long long>((n_max + qb - 1) / qb + B) * H;
-  long long grid = items * ((max_req_tokens + KB - 1) / KB);
+  const int nkv_max = (max_req_tokens + KB - 1) / KB;
+  // Pieces of cut items need scratch and the merge's launch.  Head dim 128 runs whole items
+  // from 16384 tokens on (cutting measured no faster: with two and more items per workgroup
+  // the kernel runs at the power limit); and where the items can never be worth a cut, no merge.
+  const bool may_cut = partial && (dh < 128 || n_max <= 16384) && (items > slots || nkv_max > kMinShareSteps + kCutCost);
+  const int max_units = may_cut ? gemm_max_tiles() : 0;
+  long long grid = items * nkv_max;
   if (grid > slots) grid = slots;
   if (grid < 1) grid = 1;
   grid = ((grid + kXcds - 1) / kXcds) * kXcds;
   const float scale_log2 = 1.4426950408889634f / sqrtf(static_cast<float>(dh));
 #define FD_ATTN_LAUNCH(DHV)                                                                                         \
   attn_fwd_kernel<DHV><<<grid, ACfg<DHV>::THREADS, 0, s>>>(q, kc, vc, o, D, H, cu_q, req_tok_off, B, scale_log2, partial, \
-                                                           max_units, lse);                                           \
+                                                           max_units, nkv_max, lse);                                           \
   if (max_units > 0 && B > kWalkRequests)                                                                             \
     attn_combine_kernel<DHV, true><<<grid, ACfg<DHV>::THREADS, 0, s>>>(o, D, H, cu_q, req_tok_off, B, partial,          \
-                                                                       max_units, lse);                                 \
+                                                                       max_units, nkv_max, lse);                                 \
   else if (max_units > 0)                                                                                             \
     attn_combine_kernel<DHV, false><<<grid, ACfg<DHV>::THREADS, 0, s>>>(o, D, H, cu_q, req_tok_off, B, partial,         \
-                                                                        max_units, lse)
+                                                                        max_units, nkv_max, lse)
   switch (dh) {
     case 16: FD_ATTN_LAUNCH(16); break;
     case 64: FD_ATTN_LAUNCH(64); break;
