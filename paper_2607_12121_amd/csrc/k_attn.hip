@@ -739,7 +739,7 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
         // three stages that overlap across pairs: exponents of pair pp, scaled scores
         // of pair pp + 1, bf16 pack and row sum of pair pp - 1, so no instruction waits
         // for the one before it; a job follows each pair.  The order is pinned per pair.
-        // (Packed batch, one box: 290 us with each pair's four steps in turn and reads two
+        // (Packed batch, same card: 290 us with each pair's four steps in turn and reads two
         // jobs ahead, 284 so and three ahead; image 73.6 / 72.0, video block 2424 / 2401.)
         float lsum[QG][4];   // four independent chains of row-sum dot products
 #pragma unroll
