@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "fd_common.h"
+#include "fd_rules.h"
 
 namespace {
 
@@ -21,13 +22,11 @@ int score_rows_per_chunk(int C) {
   return r < 1 ? 1 : r;
 }
 
-// Token rows per workgroup of the score: a whole region (one pass, no finalize launch)
-// when there are enough regions to fill the GPU one workgroup each, or when a region is
-// at most 16 float4 per thread of a 1024-thread workgroup; larger regions are cut.
+// Token rows per workgroup of the score: a whole region (one pass) or a chunk of one.
 int score_rows(const fd_plan* p, int C) {
-  if (p->n_regions >= 2 * fdh::num_cus() || static_cast<long long>(p->max_region_tokens) * C <= 65536)
-    return p->max_region_tokens;
-  return score_rows_per_chunk(C);
+  return fd::score_one_pass(p->n_regions, static_cast<long long>(p->max_region_tokens) * C, fdh::num_cus())
+             ? p->max_region_tokens
+             : score_rows_per_chunk(C);
 }
 
 struct BlockWs {

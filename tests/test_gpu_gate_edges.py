@@ -77,6 +77,28 @@ def test_score_one_pass_and_cut(C, size):
     np.testing.assert_allclose(score.cpu().numpy(), orc.region_score(lay, x, xp), rtol=N * C * 2.0 ** -53, atol=0)
 
 
+@pytest.mark.parametrize("C,R,size", [(64, 3, 128), (64, 3, 129), (64, 128, 256), (64, 127, 256), (64, 192, 1024), (64, 191, 1024),
+                                      (256, 1, 256), (16, 5, 4097), (64, 2, 1025)])
+def test_score_on_both_sides_of_the_pass_rule(C, R, size):
+    """R regions of exactly `size` tokens, one pass or cut, through both entry points: the cut ones
+    sum their partials in the caller's workspace and in the built-in scratch."""
+    rng = np.random.default_rng([C, R, size])
+    N = R * size
+    region = np.arange(N) // size
+    lay = orc.Layout(region, np.array([0, N]), R)
+    gh.say(f"score pass rule C={C} R={R} size={size}")
+    plan = fdl.make_plan(region.astype(np.int32), np.array([0, N], np.int32), R)
+    x, xp = (rng.standard_normal((N, C), dtype=np.float32) for _ in range(2))
+    dx, dxp = torch.from_numpy(x).cuda(), torch.from_numpy(xp).cuda()
+    got, own = (torch.full((R,), np.nan, dtype=torch.float64, device="cuda") for _ in range(2))
+    ws = torch.empty(max(fdl.fd_region_score_ws_size(plan, C), 256), dtype=torch.uint8, device="cuda")
+    fdl.fd_region_score(plan, C, dx, dxp, got, ws)
+    fdl.fd_region_score_noalloc(plan, C, dx, dxp, own)
+    # fp64 sums of size * C non-negative terms in another order
+    np.testing.assert_allclose(got.cpu().numpy(), orc.region_score(lay, x, xp), rtol=size * C * 2.0 ** -53, atol=0)
+    assert torch.equal(got, own)
+
+
 @pytest.mark.parametrize("C,sizes", [(16, [5]), (64, [127, 1, 130]), (48, [33, 700]), (256, [3, 2, 1])])
 def test_drift_update_odd_sizes(C, sizes):
     rng = np.random.default_rng([C, len(sizes)])
