@@ -23,4 +23,19 @@ FD_RULE bool score_one_pass(int regions, long long values, int cus) {
   return values <= 65536 && 4 * regions >= 3 * cus;
 }
 
+// What a cut costs, in tile-steps (1.3 us at head dim 64, 1.8 at 128): the extra pieces'
+// queries, first tiles and stores, and the merge.  Measured, us per attention, whole / cut:
+// head dim 128, 60 items of 64 key tiles 108 / 65, 24 of 16 36 / 31, 192 of 16 47 / 61, 144
+// of 2 15 / 31; head dim 64, 12 of 16 26 / 20, 16 of 8 19 / 18, 16 of 4 15 / 17.
+constexpr int kCutCost = 7;
+constexpr int kMinShareSteps = 4;   // 2, 3, 4 and 6 measured: 24 / 24 / 21 / 26 us for 48 items of 16
+
+// Shares cut items when the longest share gets shorter by more than the pieces' fixed cost;
+// otherwise every share is a run of whole items: one of the longest at most while there are items
+// for every workgroup no more than once, else up to one more than its part.
+FD_RULE bool attn_cuts(int items, long long part, int nkv_max, int G) {
+  const long long whole = items <= G ? nkv_max : part + nkv_max;
+  return (part > kMinShareSteps ? part : kMinShareSteps) + kCutCost < whole;
+}
+
 }  // namespace fd

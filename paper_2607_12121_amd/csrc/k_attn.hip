@@ -33,16 +33,15 @@
 // 2^(max - overall max) * sum (deterministic for a given grid); no workgroup
 // waits for another.  Shares are dealt to the 8 XCDs in contiguous chunks so that
 // the query tiles sharing a head's K/V run on the same L2.  Where a cut would not
-// shorten the longest share by more than it costs, and without scratch for a partial
-// per piece, shares are runs of whole items.
+// shorten the longest share by more than it costs, shares are runs of whole items.
 #include <type_traits>
 
+#include "fd_attn_sched.h"
 #include "fd_common.h"
 
 namespace {
 
-constexpr int kXcds = 8;
-constexpr int KB = 64;                    // keys per tile
+constexpr int KB = fd::kKeyTile;
 constexpr int kMaxThreads = 512;        // largest workgroup (the partial slots are per thread)
 constexpr int kMaxQG = 2;
 
@@ -146,21 +145,16 @@ FD_DEVICE bf16x8_t lds_read16(uint32_t addr) {
   return __builtin_bit_cast(bf16x8_t, *(__attribute__((address_space(3))) const u32x4_t*)(uintptr_t)addr);
 }
 
-constexpr int kMaxSchedRequests = fdh::kMaxAttnRequests;
+using fd::kXcds;
+using fd::SchedTables;
+static_assert(fd::kMaxSchedRequests == fdh::kMaxAttnRequests, "one table entry per request");
 // Up to this many requests the merge pass walks them instead of building the
 // tables (a kernel of its own, without the tables' LDS): most of its workgroups
 // only look up their share and exit, and for a handful of requests the walk
 // costs less than the table build and its barriers.
 constexpr int kWalkRequests = 16;
 
-// Per-request prefix tables of the schedule, built once per workgroup: wpre[b] =
-// tile-steps (query tiles x key tiles, one head) of the requests before b, tpre[b]
-// = their query tiles; entry B holds the totals.
-struct SchedTables {
-  long long wpre[kMaxSchedRequests + 1];
-  int tpre[kMaxSchedRequests + 1];
-};
-
+// The schedule's prefix tables, built once per workgroup.
 // One exclusive scan over the requests: each thread sums a contiguous run of them,
 // the runs' sums are scanned within each wave (shuffles) and across the waves
 // (LDS), and each thread then writes its run's prefixes.  O(B / threads + log)
@@ -219,159 +213,6 @@ FD_DEVICE void build_sched_tables(SchedTables& t, const int32_t* __restrict__ cu
   __syncthreads();
 }
 
-// A wave-uniform value read from LDS, moved to a scalar register so that the loop
-// bounds and branches derived from it stay scalar.
-FD_DEVICE int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-FD_DEVICE long long uniform(long long v) {
-  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
-  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32)));
-  return static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-// floor(q / d) for 0 <= q < 2^50, d >= 1, as a double multiply by the refined reciprocal
-// and one correction (a 64-bit integer division takes about 0.4 us of dependent code, and a
-// workgroup's first piece needed eight: 3.2 to 4.5 us of the image pass's 60)
-FD_DEVICE double reciprocal(long long d) {
-  const double x = static_cast<double>(d);
-  double r = __builtin_amdgcn_rcp(x);   // 1 ulp of single precision or better: two Newton steps
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
-}
-FD_DEVICE long long div_by(long long q, long long d, double inv) {
-  long long r = static_cast<long long>(static_cast<double>(q) * inv);
-  const long long rem = q - r * d;
-  r += rem >= d ? 1 : 0;
-  r -= rem < 0 ? 1 : 0;
-  return r;
-}
-
-// Schedule: the key tiles of every item, items head-major, form one range of
-// `work` tile-steps cut into G contiguous shares, one per workgroup, numbered so
-// that each XCD gets consecutive shares (the query tiles of a head share its K/V
-// in that XCD's L2).  With cuts the shares are equal: a share covers the end of
-// one item, whole items and the start of another, and an item covered by
-// several shares is a cut item whose pieces attn_combine_kernel merges.  A share
-// w holds at most two pieces of cut items: the continuation of an item begun in
-// an earlier share (scratch slot 2w) and the first piece of an item that goes on
-// into later shares (slot 2w + 1; when that item starts at the share's start
-// there is no continuation and slot 2w stays unused).  Without cuts every share
-// boundary is rounded up to the next item start.  Requests are found by binary
-// search in the workgroup's prefix tables.
-// What a cut costs, in tile-steps (1.3 us at head dim 64, 1.8 at 128): the extra pieces'
-// queries, first tiles and stores, and the merge.  Measured, us per attention, whole / cut:
-// head dim 128, 60 items of 64 key tiles 108 / 65, 24 of 16 36 / 31, 192 of 16 47 / 61, 144
-// of 2 15 / 31; head dim 64, 12 of 16 26 / 20, 16 of 8 19 / 18, 16 of 4 15 / 17.
-constexpr int kCutCost = 7;
-constexpr int kMinShareSteps = 4;   // 2, 3, 4 and 6 measured: 24 / 24 / 21 / 26 us for 48 items of 16
-
-template <int QB, bool TABLES>
-struct AttnSched {
-  const SchedTables* t;         // TABLES: the workgroup's prefix tables
-  const int32_t* cu_q;          // else the requests are walked
-  const int32_t* req_tok_off;
-  int B, G;               // G: shares, a multiple of the XCDs when they cut
-  int tiles;              // query tiles over all requests
-  long long work_head;    // tile-steps of one head (key tiles summed over every query tile)
-  long long work;         // ... of every head
-  long long per;          // share x starts at x * per + min(x, extra)
-  int extra;
-  bool cut;
-  bool narrow;            // work for the whole grid (head dim <= 64: pieces then store O in bf16)
-
-  FD_DEVICE AttnSched(const SchedTables* tab, const int32_t* cq, const int32_t* rto, int B_, int H, int G_,
-                      int max_units, int nkv_max)
-      : t(tab), cu_q(cq), req_tok_off(rto), B(B_), G(G_), tiles(0), work_head(0) {
-    if constexpr (TABLES) {
-      tiles = uniform(t->tpre[B]);
-      work_head = uniform(t->wpre[B]);
-    } else {
-      for (int b = 0; b < B; ++b) {
-        const int nt = (cu_q[b + 1] - cu_q[b] + QB - 1) / QB;
-        tiles += nt;
-        work_head += static_cast<long long>(nt) * ((req_tok_off[b + 1] - req_tok_off[b] + KB - 1) / KB);
-      }
-    }
-    work = work_head * H;
-    // Shares cut items when the scratch holds two partials per share and the longest share
-    // gets shorter by more than the pieces' fixed cost; otherwise every share is a run of
-    // whole items: one of the longest at most while there are items for every workgroup no
-    // more than once, else up to one more than its part.  Little work runs on as many
-    // workgroups as give each kMinShareSteps tile-steps.
-    const long long part = div_by(work, G, reciprocal(G));
-    const long long whole = static_cast<long long>(tiles) * H <= G ? nkv_max : part + nkv_max;
-    cut = max_units >= 2 * G && G % kXcds == 0 && (part > kMinShareSteps ? part : kMinShareSteps) + kCutCost < whole;
-    narrow = work >= G;
-    if (cut) {
-      const long long want = div_by(work + kMinShareSteps - 1, kMinShareSteps, 1.0 / kMinShareSteps);
-      const long long up = (want + kXcds - 1) / kXcds * kXcds;
-      if (up < G) G = static_cast<int>(up);
-    }
-    per = div_by(work, G, reciprocal(G));
-    extra = static_cast<int>(work - per * G);
-  }
-  // the share run by workgroup `blk` (G: none)
-  FD_DEVICE int share(int blk) const {
-    const int per_xcd = G / kXcds;
-    if (G % kXcds != 0) return blk;
-    return blk / kXcds < per_xcd ? (blk % kXcds) * per_xcd + blk / kXcds : G;
-  }
-  // tile-step q < work: its item's first tile-step and key tiles, head, request,
-  // the request's first query tile and the query tile
-  FD_DEVICE void locate(long long q, long long& i_start, int& nkv, int& head, int& b, int& first, int& tau) const {
-    head = static_cast<int>(div_by(q, work_head, reciprocal(work_head)));
-    long long r = q - static_cast<long long>(head) * work_head;
-    if constexpr (!TABLES) {   // few requests: walk them (requests without tile-steps are passed over)
-      b = 0;
-      first = 0;
-      nkv = 1;
-      for (; b < B; ++b) {
-        const int nt = (cu_q[b + 1] - cu_q[b] + QB - 1) / QB;
-        nkv = (req_tok_off[b + 1] - req_tok_off[b] + KB - 1) / KB;
-        const long long span = static_cast<long long>(nt) * nkv;
-        if (r < span) break;
-        r -= span;
-        first += nt;
-      }
-      const long long t = div_by(r, nkv, reciprocal(nkv));
-      tau = first + static_cast<int>(t);
-      i_start = q - (r - t * nkv);
-      return;
-    }
-    // the request: the largest b < B with wpre[b] <= r, which has tile-steps
-    // (wpre[b + 1] > r); requests without any are passed over
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (uniform(t->wpre[mid]) <= r) lo = mid; else hi = mid - 1;
-    }
-    b = lo;
-    first = uniform(t->tpre[b]);
-    const int nt = uniform(t->tpre[b + 1]) - first;
-    const long long w0 = uniform(t->wpre[b]);
-    nkv = static_cast<int>(div_by(uniform(t->wpre[b + 1]) - w0, nt, reciprocal(nt)));
-    r -= w0;
-    const long long y = div_by(r, nkv, reciprocal(nkv));
-    tau = first + static_cast<int>(y);
-    i_start = q - (r - y * nkv);
-  }
-  FD_DEVICE long long bound(long long x) const {   // first tile-step of share x (x <= G)
-    if (x >= G) return work;
-    const long long q = x * per + (x < extra ? x : extra);
-    if (cut || q >= work) return q;
-    long long i_start;
-    int nkv, head, b, first, tau;
-    locate(q, i_start, nkv, head, b, first, tau);
-    return i_start == q ? q : i_start + nkv;
-  }
-  FD_DEVICE int share_of(long long q) const {   // the share holding tile-step q (cut schedules: per >= 1)
-    const long long long_end = extra * (per + 1);   // the first `extra` shares hold one tile-step more
-    if (q < long_end) return static_cast<int>(div_by(q, per + 1, reciprocal(per + 1)));
-    return extra + static_cast<int>(div_by(q - long_end, per, reciprocal(per)));
-  }
-  // scratch slot of piece j of a cut item whose first piece is in share f
-  FD_DEVICE static int slot_of(int f, int j) { return j == 0 ? 2 * f + 1 : 2 * (f + j); }
-};
-
 // Normalised O^T block rows of one 32-query group to bf16 O (row qrow, head
 // columns col0 ...) and the query's base-2 log-sum-exp of the scaled scores
 // (softmax = exp2(s * scale_log2 - lse)); lane (l32, lg) holds query l32 and, in
@@ -395,19 +236,21 @@ FD_DEVICE void store_o(uint16_t* __restrict__ O, float* __restrict__ lse, int D,
     }
 }
 
-template <int DH>
+// CUT: the schedule may cut items.  A launch that cannot cut runs the kernel without the pieces'
+// code: 128 to 512 tokens at head dim 128 took 1 us longer with it.
+template <int DH, bool CUT>
 __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_eu(ACfg<DH>::WPE, ACfg<DH>::WPE))) void attn_fwd_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
     uint16_t* __restrict__ O, int D, int H, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ req_tok_off,
-    int B, float scale_log2, float* __restrict__ partial, int max_units, int nkv_max, float* __restrict__ lse) {
+    int B, float scale_log2, float* __restrict__ partial, int nkv_max, float* __restrict__ lse) {
   using C = ACfg<DH>;
   constexpr int DT = C::DT, KS = C::KS, KCH = C::KCH, STAGES = C::STAGES, LOADS = C::LOADS, QG = C::QG, QB = C::QB;
   __shared__ uint4 ring[STAGES][C::STAGE];
   __shared__ SchedTables tabs;
 
   build_sched_tables<C::THREADS>(tabs, cu_q, req_tok_off, B, QB);
-  const AttnSched<QB, true> sch(&tabs, cu_q, req_tok_off, B, H, static_cast<int>(gridDim.x), max_units,
-                                nkv_max);
+  using Sched = fd::AttnSched<QB, DH, true, CUT>;
+  const Sched sch(&tabs, cu_q, req_tok_off, B, H, static_cast<int>(gridDim.x), nkv_max);
   if (sch.tiles == 0) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -851,14 +694,14 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
 #pragma unroll
     for (int g = 0; g < QG; ++g) l_run[g] = half_sum(l_run[g]);
 
-    if (npieces > 1) {
+    if (CUT && npieces > 1) {
       // a piece of a cut item: O / sum and, for attn_combine_kernel, (max, sum) in fp32,
       // lane-major (quad q of thread t at word q * THREADS + t, then, past the slot's O
       // area, the (max, sum) pair of group g at float2 g * THREADS + t).  The quads are
       // fp32; where many pieces make their traffic count (head dim <= 64, work for the
       // whole grid: image 3 us) bf16, which a convex combination of V rows never leaves.
       constexpr int E = QG * (DT * 16 + 2);
-      float* slot = partial + static_cast<size_t>(AttnSched<QB, true>::slot_of(share0, piece)) * (E * C::THREADS);
+      float* slot = partial + static_cast<size_t>(Sched::slot_of(share0, piece)) * (E * C::THREADS);
       uint2* quads = reinterpret_cast<uint2*>(slot) + tid;
       fd::f32x2_t* ml = reinterpret_cast<fd::f32x2_t*>(slot + QG * DT * 16 * C::THREADS) + tid;
 #pragma unroll
@@ -895,16 +738,18 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
     int nkv, head, b, first, tau;
     sch.locate(p, i_start, nkv, head, b, first, tau);
     if (b >= B) break;   // unreachable: p < work
-    const long long i_end = i_start + nkv;
-    const int kt0 = static_cast<int>(p - i_start);
-    const int kt1 = static_cast<int>((p_end < i_end ? p_end : i_end) - i_start);
-    int f = w, l = w;
-    if (sch.cut) {
-      f = sch.share_of(i_start);
-      l = sch.share_of(i_end - 1);
+    if constexpr (!CUT) {
+      run_piece(head, tau, b, first, 0, nkv, 0, 1, w);
+      p += nkv;
+    } else {
+      const long long i_end = i_start + nkv;
+      const int kt0 = static_cast<int>(p - i_start);
+      const int kt1 = static_cast<int>((p_end < i_end ? p_end : i_end) - i_start);
+      int f = w, l = w;
+      if (sch.cut) sch.pieces_of(w, i_start, i_end, f, l);
+      run_piece(head, tau, b, first, kt0, kt1, w - f, l - f + 1, f);
+      p = i_start + kt1;
     }
-    run_piece(head, tau, b, first, kt0, kt1, w - f, l - f + 1, f);
-    p = i_start + kt1;
   }
 }
 
@@ -915,11 +760,11 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
 template <int DH, bool TABLES>
 FD_DEVICE void combine_items(uint16_t* __restrict__ O, int D, int H, const int32_t* __restrict__ cu_q,
                              const int32_t* __restrict__ req_tok_off, int B, const float* __restrict__ partial,
-                             int max_units, int nkv_max, float* __restrict__ lse, const SchedTables* tabs) {
+                             int nkv_max, float* __restrict__ lse, const SchedTables* tabs) {
   using C = ACfg<DH>;
   constexpr int DT = C::DT, QG = C::QG, QB = C::QB, E = QG * (DT * 16 + 2);
-  const AttnSched<QB, TABLES> sch(tabs, cu_q, req_tok_off, B, H, static_cast<int>(gridDim.x), max_units,
-                                nkv_max);
+  using Sched = fd::AttnSched<QB, DH, TABLES, true>;
+  const Sched sch(tabs, cu_q, req_tok_off, B, H, static_cast<int>(gridDim.x), nkv_max);
   if (sch.tiles == 0 || !sch.cut) return;
   const int x = sch.share(static_cast<int>(blockIdx.x));
   const long long p0 = sch.bound(x), p_end = sch.bound(x + 1);
@@ -930,10 +775,12 @@ FD_DEVICE void combine_items(uint16_t* __restrict__ O, int D, int H, const int32
   int nkv, head, b, first, tau;
   sch.locate(p_end - 1, i_start, nkv, head, b, first, tau);
   if (b >= B || i_start < p0 || i_start + nkv <= p_end) return;
-  const int npieces = sch.share_of(i_start + nkv - 1) - x + 1;
+  int f, l;
+  sch.pieces_of(x, i_start, i_start + nkv, f, l);
+  const int npieces = l - x + 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lg = lane >> 5;
   const int q_lo = cu_q[b] + (tau - first) * QB, q_hi = cu_q[b + 1];
-  auto slot = [&](int j) { return partial + static_cast<size_t>(AttnSched<QB, true>::slot_of(x, j)) * (E * C::THREADS); };
+  auto slot = [&](int j) { return partial + static_cast<size_t>(Sched::slot_of(x, j)) * (E * C::THREADS); };
   auto ml_of = [&](int j, int g) {
     return reinterpret_cast<const fd::f32x2_t*>(slot(j) + QG * DT * 16 * C::THREADS)[g * C::THREADS + tid];
   };
@@ -1007,13 +854,13 @@ FD_DEVICE void combine_items(uint16_t* __restrict__ O, int D, int H, const int32
 template <int DH, bool TABLES>
 __global__ __launch_bounds__(ACfg<DH>::THREADS) void attn_combine_kernel(
     uint16_t* __restrict__ O, int D, int H, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ req_tok_off,
-    int B, const float* __restrict__ partial, int max_units, int nkv_max, float* __restrict__ lse) {
+    int B, const float* __restrict__ partial, int nkv_max, float* __restrict__ lse) {
   if constexpr (TABLES) {
     __shared__ SchedTables tabs;
     build_sched_tables<ACfg<DH>::THREADS>(tabs, cu_q, req_tok_off, B, ACfg<DH>::QB);
-    combine_items<DH, true>(O, D, H, cu_q, req_tok_off, B, partial, max_units, nkv_max, lse, &tabs);
+    combine_items<DH, true>(O, D, H, cu_q, req_tok_off, B, partial, nkv_max, lse, &tabs);
   } else {
-    combine_items<DH, false>(O, D, H, cu_q, req_tok_off, B, partial, max_units, nkv_max, lse, nullptr);
+    combine_items<DH, false>(O, D, H, cu_q, req_tok_off, B, partial, nkv_max, lse, nullptr);
   }
 }
 
@@ -1031,7 +878,7 @@ size_t attn_scratch_bytes(int dh) {
 hipError_t launch_attention(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, uint16_t* o, int D, int H,
                             int dh, const int32_t* cu_q, const int32_t* req_tok_off, int B, int n_max,
                             int max_req_tokens, float* partial, float* lse, hipStream_t s) {
-  if (B < 1 || B > kMaxSchedRequests) return hipErrorInvalidValue;   // the schedule tables' size
+  if (B < 1 || B > kMaxAttnRequests) return hipErrorInvalidValue;   // the schedule tables' size
   const int occ = dh >= 128 ? ACfg<128>::OCC : ACfg<64>::OCC;
   const int slots = occ * num_cus();
   // persistent grid: the resident slots, fewer when even one key tile per share
@@ -1040,32 +887,40 @@ hipError_t launch_attention(const uint16_t* q, const uint16_t* kc, const uint16_
   const int qb = dh >= 128 ? ACfg<128>::QB : ACfg<64>::QB;
   const long long items = static_cast<long long>((n_max + qb - 1) / qb + B) * H;
   const int nkv_max = (max_req_tokens + KB - 1) / KB;
-  // Pieces of cut items need scratch and the merge's launch.  Head dim 128 runs whole items
-  // from 16384 tokens on (cutting measured no faster: with two and more items per workgroup
-  // the kernel runs at the power limit); and where the items can never be worth a cut, no merge.
-  const bool may_cut = partial && (dh < 128 || n_max <= 16384) && (items > slots || nkv_max > kMinShareSteps + kCutCost);
-  const int max_units = may_cut ? gemm_max_tiles() : 0;
   long long grid = items * nkv_max;
   if (grid > slots) grid = slots;
   if (grid < 1) grid = 1;
   grid = ((grid + kXcds - 1) / kXcds) * kXcds;
   const float scale_log2 = 1.4426950408889634f / sqrtf(static_cast<float>(dh));
-#define FD_ATTN_LAUNCH(DHV)                                                                                         \
-  attn_fwd_kernel<DHV><<<grid, ACfg<DHV>::THREADS, 0, s>>>(q, kc, vc, o, D, H, cu_q, req_tok_off, B, scale_log2, partial, \
-                                                           max_units, nkv_max, lse);                                           \
-  if (max_units > 0 && B > kWalkRequests)                                                                             \
-    attn_combine_kernel<DHV, true><<<grid, ACfg<DHV>::THREADS, 0, s>>>(o, D, H, cu_q, req_tok_off, B, partial,          \
-                                                                       max_units, nkv_max, lse);                                 \
-  else if (max_units > 0)                                                                                             \
-    attn_combine_kernel<DHV, false><<<grid, ACfg<DHV>::THREADS, 0, s>>>(o, D, H, cu_q, req_tok_off, B, partial,         \
-                                                                        max_units, nkv_max, lse)
+  // Pieces of cut items need scratch and the merge's launch.  Head dim 128 runs whole items
+  // from 16384 tokens on (cutting measured no faster: with two and more items per workgroup
+  // the kernel runs at the power limit); and where the items can never be worth a cut, no merge.
+  const bool may_cut = partial && 2 * grid <= gemm_max_tiles() && (dh < 128 || n_max <= 16384) &&
+                       (items > slots || nkv_max > fd::kMinShareSteps + fd::kCutCost);
+#define FD_ATTN_FWD(DHV, CUT)                                                                                        \
+  attn_fwd_kernel<DHV, CUT><<<grid, ACfg<DHV>::THREADS, 0, s>>>(q, kc, vc, o, D, H, cu_q, req_tok_off, B, scale_log2, \
+                                                                partial, nkv_max, lse)
+#define FD_ATTN_LAUNCH(DHV)                                                                                          \
+  if (!may_cut) {                                                                                                    \
+    FD_ATTN_FWD(DHV, false);                                                                                         \
+    break;                                                                                                           \
+  }                                                                                                                  \
+  FD_ATTN_FWD(DHV, true);                                                                                            \
+  if (B > kWalkRequests)                                                                                             \
+    attn_combine_kernel<DHV, true><<<grid, ACfg<DHV>::THREADS, 0, s>>>(o, D, H, cu_q, req_tok_off, B, partial,       \
+                                                                       nkv_max, lse);                                \
+  else                                                                                                               \
+    attn_combine_kernel<DHV, false><<<grid, ACfg<DHV>::THREADS, 0, s>>>(o, D, H, cu_q, req_tok_off, B, partial,      \
+                                                                        nkv_max, lse);                               \
+  break
   switch (dh) {
-    case 16: FD_ATTN_LAUNCH(16); break;
-    case 64: FD_ATTN_LAUNCH(64); break;
-    case 128: FD_ATTN_LAUNCH(128); break;
+    case 16: FD_ATTN_LAUNCH(16);
+    case 64: FD_ATTN_LAUNCH(64);
+    case 128: FD_ATTN_LAUNCH(128);
     default: return hipErrorInvalidValue;
   }
 #undef FD_ATTN_LAUNCH
+#undef FD_ATTN_FWD
   return hipGetLastError();
 }
 

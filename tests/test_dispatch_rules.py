@@ -1,19 +1,70 @@
 """The rules that choose a kernel variant by size (csrc/fd_rules.h), compiled for the CPU: each
-rule on both sides of its lines, at sizes where both variants were measured on an MI355X."""
+rule on both sides of its lines, at sizes where both variants were measured on an MI355X.  The
+attention's schedule (csrc/fd_attn_sched.h) runs every tile-step exactly once, whole or cut."""
 import ctypes
 import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_12121_amd", "csrc")
 CUS = 256
 
 SHIM = r"""
-#include "fd_rules.h"
+#include "fd_attn_sched.h"
+namespace {
+// Every piece of every share as attn_fwd_kernel walks them, eight numbers each: share, head,
+// query tile, request, first and last + 1 key tile, number in its item, pieces of its item.
+template <int QB, int DH, bool TABLES, bool CUT>
+int pieces(const int32_t* cu_q, const int32_t* tok, int B, int H, int G, int nkv_max, int* out, int cap, int* cut) {
+  static fd::SchedTables t;
+  t.tpre[0] = 0;
+  t.wpre[0] = 0;
+  for (int b = 0; b < B; ++b) {
+    const int nt = (cu_q[b + 1] - cu_q[b] + QB - 1) / QB;
+    t.tpre[b + 1] = t.tpre[b] + nt;
+    t.wpre[b + 1] = t.wpre[b] + static_cast<long long>(nt) * ((tok[b + 1] - tok[b] + 63) / 64);
+  }
+  const fd::AttnSched<QB, DH, TABLES, CUT> s(&t, cu_q, tok, B, H, G, nkv_max);
+  *cut = s.cut;
+  int n = 0;
+  if (s.tiles == 0) return 0;
+  for (int blk = 0; blk < G; ++blk) {
+    const int w = s.share(blk);
+    long long p = s.bound(w);
+    const long long p_end = s.bound(w + 1);
+    while (p < p_end) {
+      long long i0;
+      int nkv, head, b, first, tau;
+      s.locate(p, i0, nkv, head, b, first, tau);
+      const long long i1 = i0 + nkv, e = p_end < i1 ? p_end : i1;
+      int f = w, l = w;
+      if (s.cut) s.pieces_of(w, i0, i1, f, l);
+      if (n == cap) return -1;
+      const int row[8] = {w, head, tau, b, static_cast<int>(p - i0), static_cast<int>(e - i0), w - f, l - f + 1};
+      for (int k = 0; k < 8; ++k) out[8 * n + k] = row[k];
+      ++n;
+      p = e;
+    }
+  }
+  return n;
+}
+}  // namespace
 extern "C" {
 int score_one_pass(int regions, long long values, int cus) { return fd::score_one_pass(regions, values, cus); }
+long long div_steps(long long q, long long d) { return fd::div_steps(q, d); }
+int attn_pieces(int dh, int tables, int may_cut, const int32_t* cu_q, const int32_t* tok, int B, int H, int G, int nkv_max,
+                int* out, int cap, int* cut) {
+#define RUN(QB, DH)                                                                                                      \
+  (tables ? (may_cut ? pieces<QB, DH, true, true>(cu_q, tok, B, H, G, nkv_max, out, cap, cut)                            \
+                     : pieces<QB, DH, true, false>(cu_q, tok, B, H, G, nkv_max, out, cap, cut))                          \
+          : (may_cut ? pieces<QB, DH, false, true>(cu_q, tok, B, H, G, nkv_max, out, cap, cut)                           \
+                     : pieces<QB, DH, false, false>(cu_q, tok, B, H, G, nkv_max, out, cap, cut)))
+  return dh == 16 ? RUN(128, 16) : dh == 64 ? RUN(256, 64) : RUN(256, 128);
+#undef RUN
+}
 }
 """
 
@@ -30,6 +81,8 @@ def rules(tmp_path_factory):
                    check=True)
     lib = ctypes.CDLL(str(so))
     lib.score_one_pass.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_int]
+    lib.div_steps.argtypes = [ctypes.c_longlong] * 2
+    lib.div_steps.restype = ctypes.c_longlong
     return lib
 
 
@@ -43,3 +96,88 @@ def rules(tmp_path_factory):
 ])
 def test_score_pass(rules, regions, values, one_pass):
     assert bool(rules.score_one_pass(regions, values, CUS)) == one_pass
+
+
+def test_attention_share_bounds(rules):
+    """The multiplication that stands for the division by the share count, at every argument."""
+    for G in (8, 16, 24, 248, 256, 304, 512, 1000, 1024):
+        inv = 0xffffffff // G + 1
+        a = np.arange(G * G + 1, dtype=np.uint64)
+        assert np.array_equal((a * np.uint64(inv)) >> np.uint64(32), a // np.uint64(G))
+
+
+def test_attention_division(rules):
+    """32-bit and larger operands, on both sides of multiples of the divisor."""
+    rng = np.random.default_rng(5)
+    for qb in (1, 31, 32, 33, 50, 62):
+        for db in (1, 9, 31, 32, 33, 40):
+            for _ in range(20):
+                d = max(1, int(rng.integers(0, 1 << db)))
+                q = int(rng.integers(0, 1 << qb))
+                for v in (q, q // d * d, q // d * d + d - 1, max(0, q // d * d - 1)):
+                    assert rules.div_steps(v, d) == v // d
+
+
+def test_attention_schedule_beyond_32_bits(rules):
+    """A request of 1.4 million tokens, 40 heads: more than 2^32 tile-steps."""
+    n = np.array([0, 1_400_000], np.int32)
+    cap = 2_000_000
+    out, cut = np.zeros((cap, 8), np.int32), ctypes.c_int()
+    nk, nt = -(-1_400_000 // 64), -(-1_400_000 // 256)
+    k = rules.attn_pieces(64, 1, 1, *(a.ctypes.data_as(ctypes.c_void_p) for a in (n, n)), 1, 40, 256, nk,
+                          out.ctypes.data_as(ctypes.c_void_p), cap, ctypes.byref(cut))
+    assert nk * nt * 40 > 1 << 32 and k >= nt * 40
+    steps = (out[:k, 5] - out[:k, 4]).astype(np.int64)
+    assert steps.min() > 0 and steps.sum() == nk * nt * 40
+
+
+@pytest.mark.parametrize("seed", range(60))
+@pytest.mark.parametrize("dh", [16, 64, 128])
+def test_attention_schedule_covers_every_tile_step_once(rules, seed, dh):
+    """Random batches (requests without active rows, ragged ends, one token): whole and cut, walked
+    and from tables, every (head, query tile) runs over all its key tiles exactly once, its pieces
+    numbered in key order, each in a scratch slot of its own, and whole where nothing may be cut."""
+    rng = np.random.default_rng([seed, dh])
+    B = int(rng.choice([1, 2, 3, 17, 40]))
+    H = int(rng.choice([1, 2, 12, 16]))
+    G = int(rng.choice([8, 16, 64, 256, 512]))
+    n = np.maximum(1, np.exp(rng.uniform(0, np.log(9000 if B < 5 else 1500), B))).astype(int)
+    act = np.where(rng.random(B) < 0.2, 0, np.minimum(n, (rng.random(B) * 1.1 * n).astype(int)))
+    tok = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    cu = np.concatenate([[0], np.cumsum(act)]).astype(np.int32)
+    QB = 128 if dh == 16 else 256
+    nt, nk = -(-act // QB), -(-n // 64)
+    want = {(h, t, b): int(nk[b]) for h in range(H) for b in range(B)
+            for t in range(int(nt[:b].sum()), int(nt[:b + 1].sum()))}
+    cap = len(want) + 2 * G + 8
+    seen = []
+    for tables in (0, 1):
+        for may_cut in (0, 1):
+            out, cut = np.zeros((cap, 8), np.int32), ctypes.c_int()
+            k = rules.attn_pieces(dh, tables, may_cut, *(a.ctypes.data_as(ctypes.c_void_p) for a in (cu, tok)), B, H, G,
+                                  int(nk.max()), out.ctypes.data_as(ctypes.c_void_p), cap, ctypes.byref(cut))
+            assert 0 <= k <= cap
+            items, slots = {}, set()
+            for w, h, t, b, k0, k1, j, np_ in out[:k].tolist():
+                assert 0 <= w < G and 0 <= k0 < k1
+                items.setdefault((h, t, b), []).append((j, k0, k1, np_, w))
+                if np_ > 1:
+                    slot = 2 * (w - j) + 1 if j == 0 else 2 * w
+                    assert 0 <= slot < 2 * G and slot not in slots
+                    slots.add(slot)
+            assert set(items) == set(want)
+            for key, ps in items.items():
+                ps.sort()
+                assert [p[0] for p in ps] == list(range(len(ps))) and all(p[3] == len(ps) for p in ps)
+                assert [p[4] for p in ps] == list(range(ps[0][4], ps[0][4] + len(ps)))
+                assert ps[0][1] == 0 and ps[-1][2] == want[key]
+                assert all(a[2] == b_[1] for a, b_ in zip(ps, ps[1:]))
+                assert may_cut or len(ps) == 1
+            work = H * int((nt * nk).sum())
+            if cut.value and work >= 4 * G:   # all shares used: share w holds [floor(w work / G), floor((w + 1) work / G))
+                steps = np.zeros(G, np.int64)
+                np.add.at(steps, out[:k, 0], out[:k, 5] - out[:k, 4])
+                np.testing.assert_array_equal(steps, np.diff([w * work // G for w in range(G + 1)]))
+            seen.append((tables, may_cut, cut.value, sorted(out[:k].tolist())))
+    # the walked and the tabled schedule are the same
+    assert [s[1:] for s in seen if s[0] == 0] == [s[1:] for s in seen if s[0] == 1]
