@@ -99,7 +99,7 @@ struct AttnSched {
     split();
     if constexpr (CUT) {
       narrow = work >= G;
-      cut = G % kXcds == 0 && attn_cuts(tiles * H, per, nkv_max, G);
+      cut = G % kXcds == 0 && attn_cuts(DH, tiles * H, H, work_head, tiles, per + (extra > 0), nkv_max, G, 0);
       if (cut) {   // little work on as many workgroups as give each kMinShareSteps tile-steps
         const long long up = ((work + kMinShareSteps - 1) / kMinShareSteps + kXcds - 1) / kXcds * kXcds;
         if (up < G) {

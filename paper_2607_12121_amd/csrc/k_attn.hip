@@ -892,11 +892,9 @@ hipError_t launch_attention(const uint16_t* q, const uint16_t* kc, const uint16_
   if (grid < 1) grid = 1;
   grid = ((grid + kXcds - 1) / kXcds) * kXcds;
   const float scale_log2 = 1.4426950408889634f / sqrtf(static_cast<float>(dh));
-  // Pieces of cut items need scratch and the merge's launch.  Head dim 128 runs whole items
-  // from 16384 tokens on (cutting measured no faster: with two and more items per workgroup
-  // the kernel runs at the power limit); and where the items can never be worth a cut, no merge.
-  const bool may_cut = partial && 2 * grid <= gemm_max_tiles() && (dh < 128 || n_max <= 16384) &&
-                       (items > slots || nkv_max > fd::kMinShareSteps + fd::kCutCost);
+  // pieces of cut items need a scratch slot each, and the merge's launch
+  const bool may_cut = partial && 2 * grid <= gemm_max_tiles() &&
+                       fd::attn_may_cut(dh, H, B, n_max, max_req_tokens, qb, static_cast<int>(grid));
 #define FD_ATTN_FWD(DHV, CUT)                                                                                        \
   attn_fwd_kernel<DHV, CUT><<<grid, ACfg<DHV>::THREADS, 0, s>>>(q, kc, vc, o, D, H, cu_q, req_tok_off, B, scale_log2, \
                                                                 partial, nkv_max, lse)

@@ -54,6 +54,12 @@ int pieces(const int32_t* cu_q, const int32_t* tok, int B, int H, int G, int nkv
 }  // namespace
 extern "C" {
 int score_one_pass(int regions, long long values, int cus) { return fd::score_one_pass(regions, values, cus); }
+int attn_cuts(int dh, int tiles, int heads, long long work_head, int nkv_max, int G) {
+  return fd::attn_cuts(dh, tiles * heads, heads, work_head, tiles, (work_head * heads + G - 1) / G, nkv_max, G, 0);
+}
+int attn_may_cut(int dh, int heads, int requests, long long tokens, int max_request_tokens, int G) {
+  return fd::attn_may_cut(dh, heads, requests, tokens, max_request_tokens, 256, G);
+}
 long long div_steps(long long q, long long d) { return fd::div_steps(q, d); }
 int attn_pieces(int dh, int tables, int may_cut, const int32_t* cu_q, const int32_t* tok, int B, int H, int G, int nkv_max,
                 int* out, int cap, int* cut) {
@@ -83,6 +89,8 @@ def rules(tmp_path_factory):
     lib.score_one_pass.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_int]
     lib.div_steps.argtypes = [ctypes.c_longlong] * 2
     lib.div_steps.restype = ctypes.c_longlong
+    lib.attn_may_cut.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
+    lib.attn_cuts.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
     return lib
 
 
@@ -96,6 +104,63 @@ def rules(tmp_path_factory):
 ])
 def test_score_pass(rules, regions, values, one_pass):
     assert bool(rules.score_one_pass(regions, values, CUS)) == one_pass
+
+
+def _cuts(rules, dh, heads, batch):
+    """batch: (requests, active rows, tokens) groups."""
+    tiles = sum(n * -(-rows // 256) for n, rows, _ in batch)
+    work = sum(n * -(-rows // 256) * -(-tok // 64) for n, rows, tok in batch)
+    nkv = max(-(-tok // 64) for _, _, tok in batch)
+    may = rules.attn_may_cut(dh, heads, sum(n for n, _, _ in batch), sum(n * tok for n, _, tok in batch),
+                             max(tok for _, _, tok in batch), CUS)
+    return bool(may) and bool(rules.attn_cuts(dh, tiles, heads, work, nkv, CUS))
+
+
+@pytest.mark.parametrize("batch,cut", [
+    # whole items were no slower, and up to 1.5 times as fast as cut ones: few key tiles ...
+    ([(8, 26, 512)], False), ([(28, 150, 512)], False), ([(16, 288, 576)], False), ([(8, 230, 768)], False),
+    ([(8, 768, 768)], False), ([(28, 576, 576)], False),
+    # ... whole rounds of items, or workgroups nearly all busy with one
+    ([(16, 1024, 1024)], False), ([(8, 51, 1024)], False), ([(4, 1024, 1024)], False), ([(8, 2048, 2048)], False),
+    ([(2, 2048, 2048)], False), ([(4, 1229, 4096)], False), ([(1, 4915, 16384)], False), ([(8, 1229, 4096)], False),
+    # the largest batch: 468 items, the power limit takes the shorter share back
+    ([(1, 9828, 32760)], False),
+    # few long items, or a last round that is nearly empty
+    ([(1, 51, 1024)], True), ([(1, 1229, 4096)], True), ([(1, 2458, 8192)], True), ([(1, 1638, 32760)], True),
+    ([(1, 3276, 32760)], True), ([(1, 6552, 32760)], True), ([(1, 8192, 8192)], True), ([(2, 3072, 3072)], True),
+    ([(1, 819, 16384)], True), ([(1, 16384, 16384), (2, 1024, 1024)], True),
+])
+def test_attention_cut_head_dim_128(rules, batch, cut):
+    """12 heads of 128: the video model's."""
+    assert _cuts(rules, 128, 12, batch) == cut
+
+
+@pytest.mark.parametrize("batch,cut", [
+    ([(28, 77, 512)], False), ([(16, 1024, 1024)], False), ([(28, 512, 512)], False), ([(8, 1024, 1024)], False),
+    ([(2, 1536, 1536)], False), ([(4, 614, 2048)], False), ([(1, 16384, 16384)], False),
+    ([(1, 51, 1024)], True), ([(1, 1024, 2048)], True), ([(8, 205, 4096)], True), ([(2, 3072, 3072)], True),
+    ([(4, 1229, 4096)], True), ([(1, 9828, 32760)], True), ([(2, 512, 1024), (3, 1037, 2304), (3, 1843, 4096)], True),
+])
+def test_attention_cut_head_dim_64(rules, batch, cut):
+    """16 heads of 64: the audio model's."""
+    assert _cuts(rules, 64, 16, batch) == cut
+
+
+@pytest.mark.parametrize("dh,heads,requests,tokens,may", [
+    # the merge is not launched where no share of active rows would cut
+    (128, 12, 1, 768, False), (128, 12, 8, 1024, False), (128, 12, 28, 1024, False), (128, 12, 48, 512, False),
+    (64, 16, 16, 1024, False), (64, 16, 48, 512, False), (64, 24, 1, 768, False),
+    (128, 12, 4, 1024, False), (128, 12, 16, 1536, False), (64, 16, 8, 1024, False),
+    (128, 12, 1, 1024, True), (128, 12, 2, 1024, True), (128, 12, 4, 2048, True), (128, 12, 1, 32760, True), (64, 24, 1, 4096, True), (64, 16, 1, 2048, True),
+])
+def test_attention_may_cut(rules, dh, heads, requests, tokens, may):
+    assert bool(rules.attn_may_cut(dh, heads, requests, requests * tokens, tokens, CUS)) == may
+
+
+def test_attention_cut_counts_active_requests(rules):
+    """One active tile of a short request beside a long skipped one: nothing to cut."""
+    for dh in (64, 128):
+        assert not rules.attn_cuts(dh, 1, 12, 5, 256, CUS)
 
 
 def test_attention_share_bounds(rules):

@@ -1,6 +1,6 @@
-"""Attention where its schedule changes: items run whole (11 key tiles) or cut (12), little work on
-a few shares, cut items at head dim 16, 64 and 128, ragged last key tiles, the merge pass over more
-requests than it walks."""
+"""Attention where its schedule changes: items run whole or cut, little work on a few shares, cut
+items at head dim 16, 64 and 128, ragged last key tiles, the merge pass over more requests than it
+walks, more items than workgroups."""
 import numpy as np
 import pytest
 import torch
@@ -20,10 +20,7 @@ def _need_gpu():
     fdl.lib()
 
 
-@pytest.mark.parametrize("dh,H", [(16, 4), (64, 2), (128, 1)])
-@pytest.mark.parametrize("sizes,active", [((704,), 2), ((705,), 2), ((2048,), 1), ((1024, 65, 3000), 2), ((2048, 33), 40),
-                                          ((1500,) + (70,) * 19, 1)])
-def test_attention_schedule_edges(dh, H, sizes, active):
+def _run(dh, H, sizes, active):
     """`active` 32-token regions of each request (all of them where it has fewer)."""
     D = max(64, H * dh)
     w = small_workload("audio", requests=tuple(wl.RequestShape("seq", (n,), (32,)) for n in sizes), activity="frac",
@@ -39,8 +36,28 @@ def test_attention_schedule_edges(dh, H, sizes, active):
         hot = regions[:active]
         x_cur[np.isin(case.rmap.token_region, hot)] += 1.0
         eps[b] = 0.5 / len(hot) if len(hot) < len(regions) else 0.0
-    gh.say(f"attention schedule edges dh={dh} sizes={sizes[:3]} n={len(sizes)} active={active}")
+    gh.say(f"attention schedule edges dh={dh} H={H} sizes={sizes[:3]} n={len(sizes)} active={active}")
     g, st = gh.run_gpu(case, eps, x_cur, x_prev)
     assert g["M"] == sum(min(n, 32 * active) for n in sizes)
     o = gh.run_oracle(case, eps, x_cur, x_prev)
     gh.compare_step(case, g, o, x_cur, st)
+
+
+@pytest.mark.parametrize("dh,H", [(16, 4), (64, 2), (128, 1)])
+@pytest.mark.parametrize("sizes,active", [((704,), 2), ((705,), 2), ((2048,), 1), ((1024, 65, 3000), 2), ((2048, 33), 40),
+                                          ((1500,) + (70,) * 19, 1)])
+def test_attention_schedule_edges(dh, H, sizes, active):
+    _run(dh, H, sizes, active)
+
+
+@pytest.mark.parametrize("dh,H,sizes,active", [
+    (128, 1, (768,), 2), (128, 1, (769,), 2),            # the last size without the merge's launch, the first that cuts
+    (128, 1, (16384,), 2), (128, 1, (16385,), 2),        # cut items at any length
+    (128, 4, (3000,) + (70,) * 70, 1),                   # 284 items on 256 workgroups, mixed: cut
+    (128, 4, (130,) * 66, 5),                            # 264 items of one length: whole rounds
+    (64, 16, (1024,) * 4, 32),                           # 256 items of one length: whole, the merge finds nothing
+])
+def test_attention_cut_rule(dh, H, sizes, active):
+    """Both sides of the rule that cuts items, with items for every workgroup no more than once and
+    with more of them."""
+    _run(dh, H, sizes, active)
