@@ -41,10 +41,15 @@
 // runs on XCD blockIdx.x % 8), so the tiles one XCD runs concurrently share A
 // and B rows in its L2.
 #include "fd_common.h"
+#include "fd_gemm_rules.h"
 
 namespace {
 
 constexpr int kXcds = 8;
+using fd::choose_split;
+using fd::kMaxSplit;
+using fd::kMinSplitSteps;
+using fd::TBK;
 
 // Epilogue of one 32x32 output block held transposed in a wave's accumulator (the
 // MFMA takes the weight fragment as its first operand): lane (l32, lg) holds output
@@ -169,14 +174,6 @@ static_assert(kLargeRing >= ring_chunks<CfgLarge>() + kSideChunks && kLargeRing 
                   kLargeRing >= ring_chunks<CfgDeep>() && kLargeRing >= ring_chunks<CfgPair>() && kLargeRing * 16 <= 160 * 1024,
               "the large ring holds every shape (and the side slots past the 256x256 one)");
 
-constexpr int TBK = 64;
-constexpr int kMaxSplit = 16;
-// K-steps every split keeps.  16: a split GEMM of 64 tiles and K = 4096 runs on 256 slots instead of
-// 128 (1024 rows x 1024: 30.6 -> 24.7 us with its sum, 256 rows 27.6 -> 19.5; 24 was the line before);
-// from 12 on the QKV and out projections (K = 1024 to 1536) split too, and their sums cost more than
-// the splits give (image out-projection 20.5 -> 26.9 us).
-constexpr int kMinSplitSteps = 16;
-
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef int int32x4_t __attribute__((ext_vector_type(4)));
 
@@ -209,14 +206,6 @@ FD_DEVICE void wait_vm_barrier() {
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(N) : "memory");
 }
 
-
-// Number of K splits (identical in every WG): split only while every unit keeps
-// at least kMinSplitSteps K-steps and the units still fit the resident workgroup slots.
-FD_DEVICE int choose_split(int tiles, int nk, int slots, int max_units) {
-  int s = 1;
-  while (s < kMaxSplit && tiles * (s + 1) <= slots && tiles * (s + 1) <= max_units && nk / (s + 1) >= kMinSplitSteps) ++s;
-  return s;
-}
 
 // Epilogue of a wave's FM x FN accumulator blocks, straight from the registers:
 // acc[i][j] is the transposed 32x32 block at rows row0 + 32i, columns cw + 32j (see
@@ -550,63 +539,16 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
   }
 }
 
-// Tile shape of the two-workgroups-per-CU kernel for M rows (identical in every
-// WG): 128x128 whenever split-K applies; otherwise the shape whose rounds of tiles
-// over the resident slots cost least, a round of 128x64 / 128x128 / 128x192 tiles
-// weighted 8 / 13 / 22 (measured per-round times at 1664 rows); ties go to the
-// larger tile.  0 = 128x128, 1 = 128x192, 2 = 128x64 (three-stage ring: a round
-// costs 8 where its two-stage version cost 10).
-FD_DEVICE int small_shape(int M, int N, int K, int slots, int max_units) {
-  const int tm = (M + 127) / 128;
-  const int t128 = tm * ((N + 127) / 128);
-  if (max_units > 0 && choose_split(t128, K / TBK, slots, max_units) > 1) return 0;
-  const int r128 = (t128 + slots - 1) / slots;
-  const int r192 = (tm * ((N + 191) / 192) + slots - 1) / slots;
-  const int r64 = (tm * ((N + 63) / 64) + slots - 1) / slots;
-  const int c128 = 13 * r128, c192 = 22 * r192, c64 = 8 * r64;
-  if (c192 <= c128 && c192 <= c64) return 1;
-  if (c128 <= c64) return 0;
-  return 2;
-}
-
 template <int KIND>
 __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(fdh::GemmArgs g, int slots) {
   __shared__ uint4 ring_mem[kSmallRing];
   const int M = min(*g.m, g.n_max);
   if (M <= 0) return;
-  switch (small_shape(M, g.N, g.K, slots, g.max_units)) {
+  switch (fd::small_shape(M, g.N, g.K, slots, g.max_units)) {
     case 1: gemm_tiles<CfgWide, KIND>(g, slots, M, ring_mem); break;
     case 2: gemm_tiles<CfgNarrow, KIND>(g, slots, M, ring_mem); break;
     default: gemm_tiles<CfgSmall, KIND>(g, slots, M, ring_mem); break;
   }
-}
-
-// Tile shape of the 512-thread kernel for M rows (identical in every workgroup): 128x128
-// with split-K wherever that applies; otherwise the shape whose rounds of tiles over the
-// CUs cost least.  A round's cost is its time per K-step in 50 ns, measured at 970 to 13824
-// rows x 1536 to 6144 columns: 256x256 27, 192x256 22, 128x256 16, 128x128 10; two 128x64
-// tiles per CU 10, one 7.  Ties go to the larger tile.
-enum LargeShape { kLargeTile = 0, kTallTile = 1, kMidTile = 2, kDeepTile = 3, kPairTile = 4 };
-FD_DEVICE int large_shape(int M, int N, int K, int cus, int max_units) {
-  auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  // rounds of t tiles: a multiply (five integer divisions cost every launch half a microsecond);
-  // t is far below 2^23 and the slack far above the product's error, far below 1 / cus
-  const float inv = 1.0f / static_cast<float>(cus);
-  auto rounds = [&](int t) { return static_cast<int>(ceilf(static_cast<float>(t) * inv - 1e-4f)); };
-  const int t128 = tiles(128, 128), r64 = rounds(tiles(128, 64));
-  if (max_units > 0 && choose_split(t128, K / TBK, cus, max_units) > 1) return kDeepTile;
-  int best = kLargeTile, cost = 27 * rounds(tiles(256, 256));
-  auto consider = [&](int shape, int c) {
-    if (c < cost) {
-      best = shape;
-      cost = c;
-    }
-  };
-  consider(kTallTile, 22 * rounds(tiles(192, 256)));
-  consider(kMidTile, 16 * rounds(tiles(128, 256)));
-  consider(kDeepTile, 10 * rounds(t128));
-  consider(kPairTile, (r64 >> 1) * 10 + (r64 & 1) * 7);
-  return best;
 }
 
 template <int KIND>
@@ -614,11 +556,11 @@ __global__ __launch_bounds__(kLargeThreads, 2) void gemm_large_kernel(fdh::GemmA
   __shared__ uint4 ring_mem[kLargeRing];
   const int M = min(*g.m, g.n_max);
   if (M <= 0) return;
-  switch (large_shape(M, g.N, g.K, cus, g.max_units)) {
-    case kLargeTile: gemm_tiles<CfgLarge, KIND>(g, cus, M, ring_mem); break;
-    case kTallTile: gemm_tiles<CfgTall, KIND>(g, cus, M, ring_mem); break;
-    case kMidTile: gemm_tiles<CfgMid, KIND>(g, cus, M, ring_mem); break;
-    case kDeepTile: gemm_tiles<CfgDeep, KIND>(g, cus, M, ring_mem); break;
+  switch (fd::large_shape(M, g.N, g.K, cus, g.max_units)) {
+    case fd::kLargeTile: gemm_tiles<CfgLarge, KIND>(g, cus, M, ring_mem); break;
+    case fd::kTallTile: gemm_tiles<CfgTall, KIND>(g, cus, M, ring_mem); break;
+    case fd::kMidTile: gemm_tiles<CfgMid, KIND>(g, cus, M, ring_mem); break;
+    case fd::kDeepTile: gemm_tiles<CfgDeep, KIND>(g, cus, M, ring_mem); break;
     default: gemm_tiles<CfgPair, KIND>(g, 2 * cus, M, ring_mem); break;
   }
 }
@@ -791,16 +733,6 @@ size_t gemm_scratch_bytes() {
 }
 
 namespace {
-// Row capacity (token count of the batch) from which the 512-thread kernel is used.  The
-// active row count is only known on the device, so the choice rests on the capacity; its
-// shapes hold for few rows too.  13824 tokens of 6 requests, image dims, us per block, small
-// / large kernel: 7% active 179 / 179, 22% 378 / 355, 30% 488 / 440, 70% 1012 / 860; below
-// 8192 tokens (1664 of 4096 rows: 221 / 224) the two small workgroups per CU win.
-constexpr int kLargeTileRows = 8192;
-// Row capacity from which no GEMM splits: a split needs at most 128 tiles of 128x128, under
-// 5% of the rows here, and the sum's launch, empty otherwise, costs every call 4 us.
-constexpr int kNoSplitRows = 16384;
-
 // Persistent grid: at most the resident workgroups, at least one per unit the largest
 // unit count could need (narrowest tile, every split).
 hipError_t launch_tiled(GemmKind kind, const GemmArgs& a, int max_units, bool large, hipStream_t s) {
@@ -853,13 +785,10 @@ hipError_t launch_tiled(GemmKind kind, const GemmArgs& a, int max_units, bool la
 
 hipError_t launch_gemm(GemmKind kind, const GemmArgs& a, hipStream_t s) {
   if (a.K % TBK == 0) {
-    int max_units = a.partial ? a.max_units : 0;   // no scratch: never split
-    // the embedding, whose K-steps are few, is bound by its epilogue, which more and smaller
-    // workgroups run as well (9676 x 1536: 42 / 39 us small / large kernel, 13600 x 1024: 41 / 45)
-    const bool large = a.n_max >= (kind == GEMM_EMBED ? kNoSplitRows : kLargeTileRows) && a.N >= 1024;
+    const bool large = fd::gemm_large(a.n_max, a.N, kind == GEMM_EMBED);
+    const int max_units = a.partial && fd::gemm_may_split(a.n_max, a.N, large) ? a.max_units : 0;   // no scratch: never split
     // its bf16-output kinds send the stores of rows past M to a spare slot in the scratch
     if (large && (kind == GEMM_QKV || kind == GEMM_GELU) && !a.partial) return hipErrorInvalidValue;
-    if (a.n_max >= kNoSplitRows) max_units = 0;
     return launch_tiled(kind, a, max_units, large, s);
   }
   if (kind != GEMM_EMBED) return hipErrorInvalidValue;   // D and F are multiples of 64, only C is not

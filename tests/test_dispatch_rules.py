@@ -14,6 +14,7 @@ CUS = 256
 
 SHIM = r"""
 #include "fd_attn_sched.h"
+#include "fd_gemm_rules.h"
 namespace {
 // Every piece of every share as attn_fwd_kernel walks them, eight numbers each: share, head,
 // query tile, request, first and last + 1 key tile, number in its item, pieces of its item.
@@ -56,6 +57,13 @@ extern "C" {
 int score_one_pass(int regions, long long values, int cus) { return fd::score_one_pass(regions, values, cus); }
 int attn_cuts(int dh, int tiles, int heads, long long work_head, int nkv_max, int G) {
   return fd::attn_cuts(dh, tiles * heads, heads, work_head, tiles, (work_head * heads + G - 1) / G, nkv_max, G, 0);
+}
+int gemm_large(int n_max, int N) { return fd::gemm_large(n_max, N, false); }
+// K splits of one product
+int gemm_splits(int n_max, int M, int N, int K, int cus) {
+  const bool large = fd::gemm_large(n_max, N, false);
+  if (!fd::gemm_may_split(n_max, N, large)) return 1;
+  return fd::choose_split(((M + 127) / 128) * ((N + 127) / 128), K / fd::TBK, large ? cus : 2 * cus, 4 * cus);
 }
 int attn_may_cut(int dh, int heads, int requests, long long tokens, int max_request_tokens, int G) {
   return fd::attn_may_cut(dh, heads, requests, tokens, max_request_tokens, 256, G);
@@ -246,3 +254,16 @@ def test_attention_schedule_covers_every_tile_step_once(rules, seed, dh):
             seen.append((tables, may_cut, cut.value, sorted(out[:k].tolist())))
     # the walked and the tabled schedule are the same
     assert [s[1:] for s in seen if s[0] == 0] == [s[1:] for s in seen if s[0] == 1]
+
+
+@pytest.mark.parametrize("n_max,M,N,K,splits", [
+    # the down-projections of hidden 768 and 512, few of many rows active
+    (16384, 1600, 768, 3072, 3), (16384, 4864, 768, 3072, 2), (16383, 1600, 768, 3072, 3), (32760, 4864, 512, 4096, 3),
+    # the last layer of hidden 3072, below 16384 rows only
+    (16383, 1638, 64, 3072, 3), (32768, 1638, 64, 3072, 1),
+    # wide ones split below 16384 rows only
+    (8192, 512, 1536, 6144, 5), (16383, 512, 1536, 6144, 5), (16384, 512, 1536, 6144, 1), (4096, 1664, 1536, 6144, 3),
+    (4096, 1664, 1536, 1536, 1),
+])
+def test_gemm_splits(rules, n_max, M, N, K, splits):
+    assert rules.gemm_splits(n_max, M, N, K, CUS) == splits
