@@ -260,7 +260,8 @@ fd_status fd_adaln(const fd_dims* dims, int32_t n_blocks, int32_t n_out, int32_t
  *            the call it holds this block's queries and per-query softmax
  *            normalisers, which fd_region_importance reads
  * Errors: FD_E_UNSUPPORTED for plans of more than 1024 requests (the limit of
- * fd_select as well), FD_E_SHAPE for dims that do not fit or a small workspace.
+ * fd_select as well) and for a request whose key rows are 4 GiB or more (the
+ * batch's may be larger), FD_E_SHAPE for dims that do not fit or a small workspace.
  */
 size_t fd_block_ws_size(const fd_plan* plan, const fd_dims* dims);
 fd_status fd_block_forward(const fd_plan* plan, const fd_dims* dims, const fd_block_weights* w,
@@ -281,7 +282,7 @@ fd_status fd_block_forward(const fd_plan* plan, const fd_dims* dims, const fd_bl
  * normalisers from it, and the block's key cache as that call left it.
  *   block_ws, block_ws_bytes  device, the fd_block_forward workspace (not reused since)
  *   k_cache      device bf16 [N][D], the block's key cache
- *   idx, m       device, the active rows of fd_select
+ *   idx, m       device int32 [N] and [1], the active rows of fd_select
  *   active       device uint8 [R], this step's mask
  *   r_bar, delta device fp64 [R], updated in place (both 0 before the first step)
  *   importance   optional device fp64 [R]: R_i of active regions, NaN for skipped ones

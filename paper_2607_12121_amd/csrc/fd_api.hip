@@ -379,6 +379,11 @@ fd_status fd_block_forward(const fd_plan* plan, const fd_dims* dims, const fd_bl
     return fdh::set_error("the block supports at most %d requests per call (%d given)", fdh::kMaxAttnRequests,
                           plan->n_requests),
            FD_E_UNSUPPORTED;
+  // the attention addresses a request's key and value rows with 32-bit offsets
+  if (static_cast<long long>(plan->max_request_tokens) * dims->D * 2 >= (1LL << 32))
+    return fdh::set_error("the block supports at most 4 GiB of keys per request (%d tokens x %d given)",
+                          plan->max_request_tokens, dims->D),
+           FD_E_UNSUPPORTED;
   const BlockWs bw = carve_block_ws(plan, dims, ws);
   if (ws_bytes < bw.bytes) return fdh::set_error("block workspace too small (%zu < %zu)", ws_bytes, bw.bytes), FD_E_SHAPE;
   const int D = dims->D, F = dims->F, B = plan->n_requests, N = plan->n_tokens;

@@ -50,19 +50,20 @@ typedef int int32x4_t __attribute__((ext_vector_type(4)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 using fd::bf16x2_t;
 
+// Buffer resource of the 4 GiB from a wave-uniform base address.
 FD_DEVICE int32x4_t buffer_rsrc(const void* base) {
   const uint64_t p = reinterpret_cast<uint64_t>(base);
   int32x4_t r;
-  r.x = static_cast<int>(static_cast<uint32_t>(p));
-  r.y = static_cast<int>(static_cast<uint32_t>(p >> 32) & 0xffffu);
-  r.z = 0x7fffffff;
+  r.x = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(p)));
+  r.y = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(p >> 32) & 0xffffu));
+  r.z = -1;
   r.w = 0x00020000;
   return r;
 }
 
 // 16 bytes per lane from buffer offset voff + soff (soff wave-uniform) into LDS at
 // lds_addr + 16 * lane.
-FD_DEVICE void lds_dma16(uint32_t lds_addr, uint32_t voff, int32x4_t rsrc, uint32_t soff = 0) {
+FD_DEVICE void lds_dma16(uint32_t lds_addr, uint32_t voff, int32x4_t rsrc, uint32_t soff) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
                : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff));
@@ -260,8 +261,6 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
   // are ready, so the pair drifts apart instead of contending for the same pipe
   // at the same time (image -2%, video -1%)
   if (wave_u >= C::WAVES / 2) __builtin_amdgcn_s_setprio(1);
-  const int32x4_t rs_k = buffer_rsrc(Kc);
-  const int32x4_t rs_v = buffer_rsrc(Vc);
   const uint32_t ring_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)&ring[0][0]));
 
   // V^T operand addressing for ds_read_b64_tr_b16 (see file comment)
@@ -293,7 +292,6 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
     const int k_beg = req_tok_off[b], k_end = req_tok_off[b + 1];
     const int nkt = kt1 - kt0;
     const size_t col0 = static_cast<size_t>(head) * DH;
-    const uint32_t col2 = static_cast<uint32_t>(col0 * 2);
 
     bf16x8_t qf[QG][KS];
 #pragma unroll
@@ -308,47 +306,54 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
     }
 
     // DMA of one stage: wave-load q covers 64 consecutive chunks (RPL rows) of the K|V
-    // stage.  A tile whose keys all lie inside the request adds a wave-uniform byte
-    // offset to per-lane offsets fixed for the unit; only a ragged last tile clamps
-    // its rows per lane.
+    // stage.  The piece's first row and the head's columns are in the buffer's base (64
+    // bits: the caches may be larger than the 4 GiB that an offset reaches), the tile in a
+    // wave-uniform offset; the per-lane offsets are fixed, only a ragged last tile clamps
+    // its rows.
     constexpr int RPL = 64 / KCH, TILE_BLKS = C::TILE / 64;
+    // whether wave-load q, block blk = wave + WAVES * q of the stage, is a V block: known from q
+    // alone where the K tile is whole rounds of the waves
+    auto loads_v = [](int q, int blk) {
+      return TILE_BLKS % C::WAVES == 0 ? C::WAVES * q >= TILE_BLKS : blk >= TILE_BLKS;
+    };
     const int n_full = (k_end - k_beg) / KB;
+    const size_t row0 = static_cast<size_t>(k_beg + kt0 * KB) * D + col0;
+    const int32x4_t rs_k = buffer_rsrc(Kc + row0), rs_v = buffer_rsrc(Vc + row0);
     uint32_t dma_off[LOADS];
 #pragma unroll
     for (int q = 0; q < LOADS; ++q) {
       const int blk = wave + C::WAVES * q;
-      const bool is_v = blk >= TILE_BLKS;
+      const bool is_v = loads_v(q, blk);
       const int r = (blk - (is_v ? TILE_BLKS : 0)) * RPL + lane / KCH;   // key row within the tile
       const int c = (lane % KCH) ^ (is_v ? C::fv(r) : C::fk(r));
-      dma_off[q] = static_cast<uint32_t>(k_beg + r) * static_cast<uint32_t>(2 * D) + col2 + static_cast<uint32_t>(c * 16);
+      dma_off[q] = static_cast<uint32_t>(r) * static_cast<uint32_t>(2 * D) + static_cast<uint32_t>(c * 16);
     }
     // wave-loads q in [Q0, Q1) of key tile kt (global index): K blocks to kbuf, V
     // blocks to vbuf, 1 KB per block
     auto issue_q = [&](int kt, uint32_t kbuf, uint32_t vbuf, auto q0_tag, auto q1_tag) {
       constexpr int Q0 = decltype(q0_tag)::value, Q1 = decltype(q1_tag)::value;
+      const uint32_t soff = static_cast<uint32_t>(fd::uniform(kt - kt0)) * static_cast<uint32_t>(KB * 2) * static_cast<uint32_t>(D);
       if (kt < n_full) {
-        const uint32_t soff = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(kt * KB * 2 * D));
 #pragma unroll
         for (int q = Q0; q < Q1; ++q) {
           const int blk = wave_u + C::WAVES * q;            // wave-uniform
-          const bool is_v = blk >= TILE_BLKS;
+          const bool is_v = loads_v(q, blk);
           const uint32_t dst = is_v ? vbuf + static_cast<uint32_t>((blk - TILE_BLKS) * 64 * 16)
                                     : kbuf + static_cast<uint32_t>(blk * 64 * 16);
           lds_dma16(dst, dma_off[q], is_v ? rs_v : rs_k, soff);
         }
       } else {
-        const int k0 = k_beg + kt * KB;
+        const int last = k_end - 1 - (k_beg + kt * KB);
 #pragma unroll
         for (int q = Q0; q < Q1; ++q) {
           const int blk = wave_u + C::WAVES * q;            // wave-uniform
-          const bool is_v = blk >= TILE_BLKS;
+          const bool is_v = loads_v(q, blk);
           const int r = (blk - (is_v ? TILE_BLKS : 0)) * RPL + lane / KCH;
           const int c = (lane % KCH) ^ (is_v ? C::fv(r) : C::fk(r));
-          const int key = min(k0 + r, k_end - 1);
-          const uint32_t off = static_cast<uint32_t>(key) * static_cast<uint32_t>(2 * D) + col2 + static_cast<uint32_t>(c * 16);
+          const uint32_t off = static_cast<uint32_t>(min(r, last)) * static_cast<uint32_t>(2 * D) + static_cast<uint32_t>(c * 16);
           const uint32_t dst = is_v ? vbuf + static_cast<uint32_t>((blk - TILE_BLKS) * 64 * 16)
                                     : kbuf + static_cast<uint32_t>(blk * 64 * 16);
-          lds_dma16(dst, off, is_v ? rs_v : rs_k);
+          lds_dma16(dst, off, is_v ? rs_v : rs_k, soff);
         }
       }
     };

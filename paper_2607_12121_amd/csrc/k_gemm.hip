@@ -177,26 +177,26 @@ static_assert(kLargeRing >= ring_chunks<CfgLarge>() + kSideChunks && kLargeRing 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef int int32x4_t __attribute__((ext_vector_type(4)));
 
-// Buffer resource of a raw byte buffer (base, no stride, `bytes` in range: loads
+// Buffer resource of a raw byte buffer (base, wave-uniform, no stride, `bytes` in range: loads
 // past it return zeros).
 FD_DEVICE int32x4_t buffer_rsrc(const void* base, uint32_t bytes = 0x7fffffffu) {
   const uint64_t p = reinterpret_cast<uint64_t>(base);
   int32x4_t r;
-  r.x = static_cast<int>(static_cast<uint32_t>(p));
-  r.y = static_cast<int>(static_cast<uint32_t>(p >> 32) & 0xffffu);
+  r.x = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(p)));
+  r.y = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(p >> 32) & 0xffffu));
   r.z = static_cast<int>(bytes);
   r.w = 0x00020000;
   return r;
 }
 
-// 16 bytes per lane from buffer offset `voff` into LDS at lds_addr + 16 * lane
-// (lds_addr wave-uniform).  Issued as inline assembly so that the compiler does
+// 16 bytes per lane from buffer offset voff + soff into LDS at lds_addr + 16 * lane
+// (lds_addr and soff wave-uniform).  Issued as inline assembly so that the compiler does
 // not wait for it before unrelated LDS reads; completion is awaited explicitly
 // with s_waitcnt vmcnt before the barrier that publishes a stage.
-FD_DEVICE void lds_dma16(uint32_t lds_addr, uint32_t voff, int32x4_t rsrc) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+FD_DEVICE void lds_dma16(uint32_t lds_addr, uint32_t voff, int32x4_t rsrc, uint32_t soff = 0) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
-               : "s"(lds_addr), "v"(voff), "s"(rsrc));
+               : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff));
 }
 
 // Wait until at most N of this wave's vector-memory operations are in flight,
@@ -306,8 +306,6 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
   uint4* ring_mem = ring_all + group * (STAGES * Cfg::CHUNKS);
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
   const int l32 = lane & 31, lg = lane >> 5;
-  const int32x4_t rs_a = buffer_rsrc(g.act);
-  const int32x4_t rs_b = buffer_rsrc(g.wt);
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t ring_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)&ring_mem[0]));
 
@@ -341,25 +339,31 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
     t.nkt = ((t.split + 1) * nk) / S - t.kt0;
     return true;
   };
-  // per-lane byte offsets (k = 0) of this lane's row and source chunk in each of its wave-loads
+  // The unit's first A and B rows as buffer bases (64 bits: the operands may be larger than the
+  // 2 GiB that an offset reaches), and the per-lane byte offsets from them (k = 0) of this lane's
+  // row and source chunk in each of its wave-loads.
+  const uint16_t *base_a, *base_b;
   auto offsets = [&](const Unit& t, uint32_t (&o)[LOADS]) {
+    base_a = g.act + static_cast<size_t>(t.m0) * K;
+    base_b = g.wt + static_cast<size_t>(t.n0) * K;
 #pragma unroll
     for (int q = 0; q < LOADS; ++q) {
       const int blk = wave + WAVES * q;        // 8-row block in the concatenated A|B tile
       const int r = blk * RPW + lane / CPR;
       const int c = (lane % CPR) ^ Cfg::swz(r);
-      const int gr = (q < Cfg::LOADS_A) ? min(t.m0 + r, M - 1) : min(t.n0 + (r - BM), N - 1);
-      o[q] = static_cast<uint32_t>((static_cast<size_t>(gr) * K + c * 8) * 2);   // chunk = 8 bf16
+      const int gr = (q < Cfg::LOADS_A) ? min(r, M - 1 - t.m0) : min(r - BM, N - 1 - t.n0);
+      o[q] = (static_cast<uint32_t>(gr) * static_cast<uint32_t>(K) + static_cast<uint32_t>(c * 8)) * 2;   // chunk = 8 bf16
     }
   };
   // wave-loads [q0, q1) of K-step kt of a unit (offsets o, first K-step kt0) into stage st
   auto issue_q = [&](const uint32_t (&o)[LOADS], int kt0, int kt, int st, int q0, int q1) {
     const uint32_t buf = ring_base + static_cast<uint32_t>(st * Cfg::CHUNKS * 16);
     const uint32_t kb = static_cast<uint32_t>((kt0 + kt) * BK * 2);
+    const int32x4_t rs_a = buffer_rsrc(base_a), rs_b = buffer_rsrc(base_b);
 #pragma unroll
     for (int q = 0; q < LOADS; ++q)
       if (q >= q0 && q < q1)
-        lds_dma16(buf + static_cast<uint32_t>((wave_u + WAVES * q) * 64 * 16), o[q] + kb, q < Cfg::LOADS_A ? rs_a : rs_b);
+        lds_dma16(buf + static_cast<uint32_t>((wave_u + WAVES * q) * 64 * 16), o[q], q < Cfg::LOADS_A ? rs_a : rs_b, kb);
   };
   auto prologue = [&](const Unit& t, const uint32_t (&o)[LOADS]) {
 #pragma unroll

@@ -110,6 +110,11 @@ def test_entry_points_validate_before_launch():
     many = fdl.FdPlan(2050, 1025, 1025, 2, 2, *([0x1000] * 6))
     assert lib.fd_block_forward(ctypes.byref(many), ctypes.byref(d), ctypes.byref(w), *args) == 3
     assert b"1024 requests" in lib.fd_last_error()
+    # a request of 4 GiB of keys (the last size below it is only too large for this workspace)
+    d_wide = fdl.FdDims(64, 8192, 64, 128, 64)
+    for tokens, status in ((1 << 18, 3), ((1 << 18) - 1, 2)):
+        long = fdl.FdPlan(tokens, 1, 1, tokens, tokens, *([0x1000] * 6))
+        assert lib.fd_block_forward(ctypes.byref(long), ctypes.byref(d_wide), ctypes.byref(w), *small) == status
     # select: bad gate parameters, too many regions
     g = fdl.FdGate(-1.0, 0)
     assert lib.fd_select(ctypes.byref(plan), *([0x1000] * 2), g, *([0x1000] * 7), None) == 1
