@@ -468,17 +468,25 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
           for (int j = 0; j < FN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ks & 1][j], a[ks & 1][i], acc[i][j], 0, 0, 0);
       }
-      // schedule: first fragments, then per k16 step one next-step read after each of
-      // the first FM + FN MFMAs, then the remaining MFMAs
+      // schedule: first fragments, then per k16 step one next-step read after each of the
+      // first FM + FN MFMAs, then the remaining MFMAs; with fewer MFMAs than reads (64-row by
+      // 32-column waves), every read after the first MFMA, so that they run beside the others
+      // (128x64 and 128x128 tiles of 512 threads: 1 to 3% less per product than one after each)
       __builtin_amdgcn_sched_group_barrier(0x100, FM + FN, 0);
 #pragma unroll
       for (int ks = 0; ks < BK / 16 - 1; ++ks) {
-#pragma unroll
-        for (int x = 0; x < FM + FN; ++x) {
+        if constexpr (FM * FN < FM + FN) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, FM + FN, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - 1, 0);
+        } else {
+#pragma unroll
+          for (int x = 0; x < FM + FN; ++x) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          }
+          if constexpr (FM * FN > FM + FN) __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - (FM + FN), 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - (FM + FN), 0);
       }
       __builtin_amdgcn_sched_group_barrier(0x008, FM * FN, 0);
     }
