@@ -61,6 +61,14 @@ FD_DEVICE int32x4_t buffer_rsrc(const void* base) {
   return r;
 }
 
+// The resource in scalar registers that a load in inline assembly may read at once: the compiler
+// may have moved it there with vector instructions, and does not know that a vector memory
+// instruction must not follow those within five wait states.
+FD_DEVICE int32x4_t settled(int32x4_t r) {
+  asm volatile("s_nop 4" : "+s"(r));
+  return r;
+}
+
 // 16 bytes per lane from buffer offset voff + soff (soff wave-uniform) into LDS at
 // lds_addr + 16 * lane.
 FD_DEVICE void lds_dma16(uint32_t lds_addr, uint32_t voff, int32x4_t rsrc, uint32_t soff) {
@@ -318,7 +326,7 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
     };
     const int n_full = (k_end - k_beg) / KB;
     const size_t row0 = static_cast<size_t>(k_beg + kt0 * KB) * D + col0;
-    const int32x4_t rs_k = buffer_rsrc(Kc + row0), rs_v = buffer_rsrc(Vc + row0);
+    const int32x4_t rs_k = settled(buffer_rsrc(Kc + row0)), rs_v = settled(buffer_rsrc(Vc + row0));
     uint32_t dma_off[LOADS];
 #pragma unroll
     for (int q = 0; q < LOADS; ++q) {

@@ -189,6 +189,14 @@ FD_DEVICE int32x4_t buffer_rsrc(const void* base, uint32_t bytes = 0x7fffffffu) 
   return r;
 }
 
+// The resource in scalar registers that a load in inline assembly may read at once: the compiler
+// may have moved it there with vector instructions, and does not know that a vector memory
+// instruction must not follow those within five wait states.
+FD_DEVICE int32x4_t settled(int32x4_t r) {
+  asm volatile("s_nop 4" : "+s"(r));
+  return r;
+}
+
 // 16 bytes per lane from buffer offset voff + soff into LDS at lds_addr + 16 * lane
 // (lds_addr and soff wave-uniform).  Issued as inline assembly so that the compiler does
 // not wait for it before unrelated LDS reads; completion is awaited explicitly
@@ -355,19 +363,18 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
       o[q] = (static_cast<uint32_t>(gr) * static_cast<uint32_t>(K) + static_cast<uint32_t>(c * 8)) * 2;   // chunk = 8 bf16
     }
   };
-  // wave-loads [q0, q1) of K-step kt of a unit (offsets o, first K-step kt0) into stage st
-  auto issue_q = [&](const uint32_t (&o)[LOADS], int kt0, int kt, int st, int q0, int q1) {
+  // the wave-loads of K-step kt of a unit (bases rs_a and rs_b, offsets o, first K-step kt0) into stage st
+  auto issue = [&](const int32x4_t& rs_a, const int32x4_t& rs_b, const uint32_t (&o)[LOADS], int kt0, int kt, int st) {
     const uint32_t buf = ring_base + static_cast<uint32_t>(st * Cfg::CHUNKS * 16);
     const uint32_t kb = static_cast<uint32_t>((kt0 + kt) * BK * 2);
-    const int32x4_t rs_a = buffer_rsrc(base_a), rs_b = buffer_rsrc(base_b);
 #pragma unroll
     for (int q = 0; q < LOADS; ++q)
-      if (q >= q0 && q < q1)
-        lds_dma16(buf + static_cast<uint32_t>((wave_u + WAVES * q) * 64 * 16), o[q], q < Cfg::LOADS_A ? rs_a : rs_b, kb);
+      lds_dma16(buf + static_cast<uint32_t>((wave_u + WAVES * q) * 64 * 16), o[q], q < Cfg::LOADS_A ? rs_a : rs_b, kb);
   };
   auto prologue = [&](const Unit& t, const uint32_t (&o)[LOADS]) {
+    const int32x4_t rs_a = settled(buffer_rsrc(base_a)), rs_b = settled(buffer_rsrc(base_b));
 #pragma unroll
-    for (int p = 0; p < STAGES - 1; ++p) issue_q(o, t.kt0, min(p, t.nkt - 1), p, 0, LOADS);
+    for (int p = 0; p < STAGES - 1; ++p) issue(rs_a, rs_b, o, t.kt0, min(p, t.nkt - 1), p);
   };
   // the bias of this lane's columns (split 0 only; the accumulators start there),
   // or, with overlap, zeros, and the tile's bias (wave 0) and row tokens (wave 1, QKV)
@@ -433,6 +440,7 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
         }
 
     const int nkt = cur.nkt, kt0 = cur.kt0;
+    const int32x4_t rs_a = settled(buffer_rsrc(base_a)), rs_b = settled(buffer_rsrc(base_b));   // kept for the K loop
     for (int it = 0; it < nkt; ++it) {
       // exactly STAGES - 2 younger stages (and, in the first step, the previous
       // unit's epilogue stores) are in flight: stage `it` has landed for every wave
@@ -442,7 +450,7 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
         wait_vm_barrier<(STAGES - 2) * LOADS>();
       // refill the slot every wave finished reading before this barrier (a repeat at the tail)
       const int kt_next = min(it + STAGES - 1, nkt - 1), st_next = (it + STAGES - 1) % STAGES;
-      issue_q(off, kt0, kt_next, st_next, 0, LOADS);
+      issue(rs_a, rs_b, off, kt0, kt_next, st_next);
       const uint4* sm = ring_mem + (it % STAGES) * Cfg::CHUNKS;
       bf16x8_t a[2][FM], b[2][FN];
       auto frag = [&](int ks, int slot) {
