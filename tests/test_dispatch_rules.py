@@ -59,6 +59,8 @@ int attn_cuts(int dh, int tiles, int heads, long long work_head, int nkv_max, in
   return fd::attn_cuts(dh, tiles * heads, heads, work_head, tiles, (work_head * heads + G - 1) / G, nkv_max, G, 0);
 }
 int gemm_large(int n_max, int N) { return fd::gemm_large(n_max, N, false); }
+int large_shape(int M, int N, int K, int cus) { return fd::large_shape(M, N, K, cus, 4 * cus); }
+int small_shape(int M, int N, int K, int cus) { return fd::small_shape(M, N, K, 2 * cus, 4 * cus); }
 // K splits of one product
 int gemm_splits(int n_max, int M, int N, int K, int cus) {
   const bool large = fd::gemm_large(n_max, N, false);
@@ -267,3 +269,25 @@ def test_attention_schedule_covers_every_tile_step_once(rules, seed, dh):
 ])
 def test_gemm_splits(rules, n_max, M, N, K, splits):
     assert rules.gemm_splits(n_max, M, N, K, CUS) == splits
+
+
+LARGE, TALL, MID, DEEP, PAIR = range(5)
+
+
+@pytest.mark.parametrize("M,N,K,shape", [
+    (9728, 4608, 1536, LARGE), (8200, 3072, 1024, LARGE), (8200, 1024, 1024, TALL), (3280, 3072, 1024, TALL), (3280, 2048, 1024, MID),
+    (1025, 3072, 1024, DEEP), (25, 1024, 2048, DEEP), (25, 3072, 1024, PAIR), (1025, 1024, 1024, PAIR),
+    # widths of an odd number of 64 columns: more units than workgroups, so that both tiles of a pair have work
+    (1280, 3264, 1088, PAIR), (2560, 3264, 1088, PAIR), (3712, 1088, 1088, PAIR), (7424, 1088, 1088, PAIR),
+])
+def test_large_gemm_shape(rules, M, N, K, shape):
+    assert rules.large_shape(M, N, K, CUS) == shape
+
+
+@pytest.mark.parametrize("M,N,K,shape", [(1664, 6144, 1536, 1), (1664, 4608, 1536, 0), (1664, 1536, 1536, 2), (4096, 6144, 1536, 0), (1664, 1536, 6144, 0)])
+def test_small_gemm_shape(rules, M, N, K, shape):
+    assert rules.small_shape(M, N, K, CUS) == shape
+
+
+def test_gemm_kernel_lines(rules):
+    assert not rules.gemm_large(8191, 1024) and rules.gemm_large(8192, 1024) and not rules.gemm_large(1 << 20, 1023)

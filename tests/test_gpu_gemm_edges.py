@@ -1,6 +1,7 @@
 """The GEMM variants at the sizes where they change: the embedding with channel counts
 that are and are not a multiple of 64, at the edges of its 128-row tiles; the down-projection where its split count changes; every
-tile shape of the long batches' kernel."""
+tile shape of the long batches' kernel, its pairs of tiles with work in both groups, and the row
+capacity from which it runs."""
 import numpy as np
 import pytest
 import torch
@@ -65,17 +66,46 @@ def test_block_split_edges(F, tokens, frac):
 @pytest.mark.parametrize("requests,region,active", [(1, 25, 1), (1, 25, 41), (82, 20, 2), (82, 20, 5)])
 def test_large_kernel_shapes(requests, region, active):
     """8200 tokens at hidden 1024 run the 512-thread kernel.  `active` regions per request: 25 rows
-    (pairs of 128x64 tiles, the second group of most workgroups without a unit; the down-projection's
-    128x128 tiles split in two), 1025 rows (128x128 with a last tile of one row, pairs), 3280
-    (192x256 and 128x256, ragged last tiles) and 8200 (256x256)."""
-    w = small_workload("audio", requests=tuple(wl.RequestShape("seq", (8200 // requests,), (region,)) for _ in range(requests)),
-                       activity="count", activity_args=(active,), L=1, D=1024, H=16, dh=64, F=2048)
+    (128x64 tiles, the second group of every workgroup without a unit; the down-projection's 128x128
+    tiles split in two), 1025 rows (128x128 with a last tile of one row, 128x64), 3280 (192x256 and
+    128x256, ragged last tiles) and 8200 (256x256)."""
+    _shapes(requests, region, active, 8200, 1024, 2048)
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("active", [10, 20, 29, 58])
+def test_large_kernel_pairs(active):
+    """Hidden 1088 (columns an odd number of 64s) runs two 128x64 tiles per workgroup: QKV at 1280 rows
+    (510 units: the second group of two workgroups has none) and 2560 (1020 units, two each, ends
+    unequal), the out- and down-projections at 3712 (493) and 7424 rows (986)."""
+    _shapes(1, 128, active, 8320, 1088, 1088)
+
+
+def _shapes(requests, region, active, tokens, D, F):
+    w = small_workload("audio", requests=tuple(wl.RequestShape("seq", (tokens // requests,), (region,)) for _ in range(requests)),
+                       activity="count", activity_args=(active,), L=1, D=D, H=D // 64, dh=64, F=F)
     case = gh.make_case("audio", workload=w)
-    eps = np.zeros(requests) if active == 5 else case.inp.eps
-    gh.say(f"large kernel shapes: {requests} requests, {active} active regions each")
+    eps = np.zeros(requests) if (requests, active) == (82, 5) else case.inp.eps
+    gh.say(f"large kernel shapes: D={D}, {requests} requests, {active} active regions each")
     g, st = gh.run_gpu(case, eps, case.inp.x_cur, case.inp.x_prev)
     M = requests * active * region
     assert g["M"] == M
     rows = np.unique(np.concatenate([[0, M - 1], np.random.default_rng(3).choice(M, min(M, 126), replace=False)]))
     o = gh.run_oracle(case, eps, case.inp.x_cur, case.inp.x_prev, sample_rows=rows)
+    gh.compare_step(case, g, o, case.inp.x_cur, st)
+
+
+@pytest.mark.parametrize("tokens", [8191, 8192])
+@pytest.mark.parametrize("active", [1, 30])
+def test_large_kernel_line(tokens, active):
+    """One token on either side of the capacity from which the 512-thread kernel runs, few rows
+    (the down-projection's split) and more."""
+    w = small_workload("audio", requests=(wl.RequestShape("seq", (tokens,), (32,)),), activity="count",
+                       activity_args=(active,), L=1, D=1024, H=16, dh=64, F=2048)
+    case = gh.make_case("audio", workload=w)
+    gh.say(f"large kernel line: {tokens} tokens, {active} active regions")
+    g, st = gh.run_gpu(case, case.inp.eps, case.inp.x_cur, case.inp.x_prev)
+    M = g["M"]
+    rows = np.unique(np.concatenate([[0, M - 1], np.random.default_rng(3).choice(M, min(M, 62), replace=False)]))
+    o = gh.run_oracle(case, case.inp.eps, case.inp.x_cur, case.inp.x_prev, sample_rows=rows)
     gh.compare_step(case, g, o, case.inp.x_cur, st)
