@@ -51,6 +51,10 @@ using fd::kMaxSplit;
 using fd::kMinSplitSteps;
 using fd::TBK;
 
+// Four floats at any float's address: the position table and the outputs of the embedding and the
+// last layer need no alignment of their own (the accesses stay 16 bytes wide).
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+
 // Epilogue of one 32x32 output block held transposed in a wave's accumulator (the
 // MFMA takes the weight fragment as its first operand): lane (l32, lg) holds output
 // row `row` and, in registers 4q .. 4q+3, columns c_q = cb + 8q + 4lg .. +3.  Every
@@ -116,12 +120,9 @@ FD_DEVICE void epilogue_block(const fdh::GemmArgs& g, bool row_ok, int row, int 
     for (int q = 0; q < 4; ++q) {
       const int c = cb + 8 * q + 4 * lg;
       if (!row_ok || c >= N) continue;
-      float4 r = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-      if constexpr (KIND == fdh::GEMM_EMBED) {
-        const float4 pp = *reinterpret_cast<const float4*>(g.pos + static_cast<size_t>(tok) * N + c);
-        r.x += pp.x; r.y += pp.y; r.z += pp.z; r.w += pp.w;
-      }
-      *reinterpret_cast<float4*>(out + c) = r;
+      f32x4u_t r = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+      if constexpr (KIND == fdh::GEMM_EMBED) r += *reinterpret_cast<const f32x4u_t*>(g.pos + static_cast<size_t>(tok) * N + c);
+      *reinterpret_cast<f32x4u_t*>(out + c) = r;
     }
   }
 }

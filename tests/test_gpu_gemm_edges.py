@@ -49,6 +49,31 @@ def test_embed_edges(C, M, N, D):
     assert np.all(got[M:] == -7.0)
 
 
+@pytest.mark.parametrize("C", [48, 64])
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_embed_unaligned_tables(C, shift):
+    """A position table and an output that start `shift` floats past a 16-byte line: the same bits
+    as aligned ones."""
+    M, N, D = 129, 200, 192
+    gh.say(f"embed unaligned C={C} shift={shift}")
+    rng = np.random.default_rng([C, shift])
+    dims = fdl.dims(C, D, D // 64, 64, 64)
+    plan = fdl.make_plan(np.zeros(N, np.int32), np.array([0, N], np.int32), 1)
+    idx = torch.zeros(N, dtype=torch.int32, device="cuda")
+    idx[:M] = torch.from_numpy(np.sort(rng.permutation(N)[:M]).astype(np.int32)).cuda()
+    xa, w = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)).to(torch.bfloat16).cuda() for s in ((N, C), (D, C)))
+    b, pos = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)).cuda() for s in ((D,), (N, D)))
+    m = torch.tensor([M], dtype=torch.int32, device="cuda")
+    out = []
+    for s in (0, shift):
+        p, h = (torch.zeros(N * D + s, device="cuda")[s:].view(N, D) for _ in range(2))
+        assert p.data_ptr() % 16 == 4 * s and h.data_ptr() % 16 == 4 * s
+        p.copy_(pos)
+        fdl.fd_embed(plan, dims, xa, w, b, p, idx, m, h)
+        out.append(h[:M].clone())
+    assert torch.equal(*out)
+
+
 @pytest.mark.parametrize("F", [1984, 2048, 3072])
 @pytest.mark.parametrize("tokens,frac", [((40,), 1.0), ((129, 300), 0.5)])
 def test_block_split_edges(F, tokens, frac):
