@@ -61,15 +61,9 @@ FD_DEVICE int row_request(const int32_t* __restrict__ cu_q, int B, int i) {
   return lo;
 }
 
-// GELU, tanh form: z/2 (1 + tanh(u)), u = sqrt(2/pi) (z + 0.044715 z^3).  Uses the
-// identity (1 + tanh(u)) / 2 = 1 / (1 + exp(-2u)), i.e. one exponential and one division.
-FD_DEVICE float gelu_tanh(float z) {
-  const float k2 = 1.5957691216057308f;  // 2 sqrt(2/pi)
-  const float t = k2 * (z + 0.044715f * z * z * z);
-  return z / (1.0f + __expf(-t));
-}
-// The same GELU with hardware exp2 and reciprocal (about 2 ulp): used in the MLP
-// epilogue, whose result is rounded to bf16 right after.
+// GELU, tanh form: z/2 (1 + tanh(u)), u = sqrt(2/pi) (z + 0.044715 z^3).  Uses the identity
+// (1 + tanh(u)) / 2 = 1 / (1 + exp(-2u)) with hardware exp2 and reciprocal (about 2 ulp): its
+// only use is the MLP epilogue, whose result is rounded to bf16 right after.
 FD_DEVICE float gelu_tanh_fast(float z) {
   const float k2l = 2.302208198144325f;  // 2 sqrt(2/pi) log2(e)
   const float t = k2l * (z + 0.044715f * z * z * z);

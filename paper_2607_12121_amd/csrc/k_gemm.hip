@@ -40,6 +40,8 @@
 // Work units are dealt to the 8 XCDs in contiguous chunks of tile order (a WG
 // runs on XCD blockIdx.x % 8), so the tiles one XCD runs concurrently share A
 // and B rows in its L2.
+#include <type_traits>
+
 #include "fd_common.h"
 #include "fd_gemm_rules.h"
 
@@ -765,16 +767,6 @@ hipError_t launch_tiled(GemmKind kind, const GemmArgs& a, int max_units, bool la
   long long grid = tiles_max * (max_units > 0 ? kMaxSplit : 1);
   if (grid > slots) grid = slots;
   grid = ((grid + kXcds - 1) / kXcds) * kXcds;
-#define FD_GEMM_LAUNCH(K)                                                                      \
-  if (large)                                                                                   \
-    gemm_large_kernel<K><<<grid, kLargeThreads, 0, s>>>(g, slots);                             \
-  else                                                                                         \
-    gemm_small_kernel<K><<<grid, kSmallThreads, 0, s>>>(g, slots);
-#define FD_REDUCE_LAUNCH(K)                                                                    \
-  if (large)                                                                                   \
-    splitk_reduce_kernel<K, CfgDeep><<<red_grid, CfgDeep::THREADS, 0, s>>>(g, slots);          \
-  else                                                                                         \
-    splitk_reduce_kernel<K, CfgSmall><<<red_grid, CfgSmall::THREADS, 0, s>>>(g, slots);
   // the split-K reduction, launched whenever K is long enough for a split (it
   // returns at once when the device-side M gave S = 1)
   const bool may_split = max_units > 0 && (a.K / TBK) >= 2 * kMinSplitSteps;
@@ -782,24 +774,26 @@ hipError_t launch_tiled(GemmKind kind, const GemmArgs& a, int max_units, bool la
   const long long red_units = static_cast<long long>((a.n_max + 127) / 128) * ((a.N + 127) / 128);
   const int red_grid = static_cast<int>(red_units < slots / 2 ? red_units : slots / 2) *
                        (large ? CfgDeep::FM * CfgDeep::FN : CfgSmall::FM * CfgSmall::FN);
-  switch (kind) {
-    case GEMM_QKV: FD_GEMM_LAUNCH(GEMM_QKV) break;
-    case GEMM_RESID: FD_GEMM_LAUNCH(GEMM_RESID) break;
-    case GEMM_GELU: FD_GEMM_LAUNCH(GEMM_GELU) break;
-    case GEMM_EMBED: FD_GEMM_LAUNCH(GEMM_EMBED) break;
-    case GEMM_OUT: FD_GEMM_LAUNCH(GEMM_OUT) break;
-  }
-  if (may_split) {
-    switch (kind) {
-      case GEMM_QKV: FD_REDUCE_LAUNCH(GEMM_QKV) break;
-      case GEMM_RESID: FD_REDUCE_LAUNCH(GEMM_RESID) break;
-      case GEMM_GELU: FD_REDUCE_LAUNCH(GEMM_GELU) break;
-      case GEMM_EMBED: FD_REDUCE_LAUNCH(GEMM_EMBED) break;
-      case GEMM_OUT: FD_REDUCE_LAUNCH(GEMM_OUT) break;
+  auto run = [&](auto kind_tag) {
+    constexpr int K = decltype(kind_tag)::value;
+    if (!large) {
+      gemm_small_kernel<K><<<grid, kSmallThreads, 0, s>>>(g, slots);
+      // the embedding's K (at most 256 channels) is too short to split
+      if constexpr (K != GEMM_EMBED)
+        if (may_split) splitk_reduce_kernel<K, CfgSmall><<<red_grid, CfgSmall::THREADS, 0, s>>>(g, slots);
+    } else if constexpr (K != GEMM_OUT) {   // the last layer's columns (the channels) are too few
+      gemm_large_kernel<K><<<grid, kLargeThreads, 0, s>>>(g, slots);
+      if constexpr (K != GEMM_EMBED)
+        if (may_split) splitk_reduce_kernel<K, CfgDeep><<<red_grid, CfgDeep::THREADS, 0, s>>>(g, slots);
     }
+  };
+  switch (kind) {
+    case GEMM_QKV: run(std::integral_constant<int, GEMM_QKV>{}); break;
+    case GEMM_RESID: run(std::integral_constant<int, GEMM_RESID>{}); break;
+    case GEMM_GELU: run(std::integral_constant<int, GEMM_GELU>{}); break;
+    case GEMM_EMBED: run(std::integral_constant<int, GEMM_EMBED>{}); break;
+    case GEMM_OUT: run(std::integral_constant<int, GEMM_OUT>{}); break;
   }
-#undef FD_GEMM_LAUNCH
-#undef FD_REDUCE_LAUNCH
   return hipGetLastError();
 }
 }  // namespace
@@ -809,7 +803,7 @@ hipError_t launch_gemm(GemmKind kind, const GemmArgs& a, hipStream_t s) {
     const bool large = fd::gemm_large(a.n_max, a.N, kind == GEMM_EMBED);
     const int max_units = a.partial && fd::gemm_may_split(a.n_max, a.N, large) ? a.max_units : 0;   // no scratch: never split
     // its bf16-output kinds send the stores of rows past M to a spare slot in the scratch
-    if (large && (kind == GEMM_QKV || kind == GEMM_GELU) && !a.partial) return hipErrorInvalidValue;
+    if (large && (kind == GEMM_OUT || ((kind == GEMM_QKV || kind == GEMM_GELU) && !a.partial))) return hipErrorInvalidValue;
     return launch_tiled(kind, a, max_units, large, s);
   }
   if (kind != GEMM_EMBED) return hipErrorInvalidValue;   // D and F are multiples of 64, only C is not
