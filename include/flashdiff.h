@@ -260,8 +260,9 @@ fd_status fd_adaln(const fd_dims* dims, int32_t n_blocks, int32_t n_out, int32_t
  *            the call it holds this block's queries and per-query softmax
  *            normalisers, which fd_region_importance reads
  * Errors: FD_E_UNSUPPORTED for plans of more than 1024 requests (the limit of
- * fd_select as well) and for a request whose key rows are 4 GiB or more (the
- * batch's may be larger), FD_E_SHAPE for dims that do not fit or a small workspace.
+ * fd_select as well), for a request whose key rows are 4 GiB or more (the batch's
+ * may be larger) and for one product's weights of 2 GiB or more, FD_E_SHAPE for dims
+ * that do not fit or a small workspace.
  */
 size_t fd_block_ws_size(const fd_plan* plan, const fd_dims* dims);
 fd_status fd_block_forward(const fd_plan* plan, const fd_dims* dims, const fd_block_weights* w,

@@ -379,6 +379,11 @@ fd_status fd_block_forward(const fd_plan* plan, const fd_dims* dims, const fd_bl
     return fdh::set_error("the block supports at most %d requests per call (%d given)", fdh::kMaxAttnRequests,
                           plan->n_requests),
            FD_E_UNSUPPORTED;
+  // the tile loads address the weights of one product with 31-bit offsets
+  const long long widest = dims->F > 3LL * dims->D ? dims->F : 3LL * dims->D;
+  if (2 * widest * dims->D > fdh::kMaxGemmBytes)
+    return fdh::set_error("the block supports weights below 2 GiB per product (%lld x %d given)", widest, dims->D),
+           FD_E_UNSUPPORTED;
   // the attention addresses a request's key and value rows with 32-bit offsets
   if (static_cast<long long>(plan->max_request_tokens) * dims->D * 2 >= (1LL << 32))
     return fdh::set_error("the block supports at most 4 GiB of keys per request (%d tokens x %d given)",

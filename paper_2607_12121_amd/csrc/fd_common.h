@@ -114,6 +114,7 @@ struct GemmArgs {
   const uint16_t* wt;    // [N][K] bf16 weights
   const float* bias;     // [N]
   int n_max;             // row capacity (upper bound of M)
+  int row0;              // set per launch: rows before the first of this launch (of M and the request offsets)
   const int32_t* m;      // device active row count
   int N, K;
   // epilogue operands
@@ -130,6 +131,13 @@ struct GemmArgs {
 // Bytes of split-K scratch the tiled GEMM needs (fp32 partial tiles), for any shape.
 size_t gemm_scratch_bytes();
 int gemm_max_tiles();
+// The tile loads' offsets stay below 2 GiB: the weights of a product must, and a launch takes as
+// many activation rows as do, in whole tiles where that is a tile or more.
+constexpr long long kMaxGemmBytes = 0x7fffffff;
+constexpr int gemm_rows_per_launch(int K) {
+  const int rows = static_cast<int>(kMaxGemmBytes / (2LL * K));
+  return rows >= 256 ? rows / 256 * 256 : rows;
+}
 hipError_t launch_gemm(GemmKind kind, const GemmArgs& a, hipStream_t s);
 
 // Requests per attention launch (its schedule tables live in LDS).

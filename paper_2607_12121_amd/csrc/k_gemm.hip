@@ -180,34 +180,26 @@ static_assert(kLargeRing >= ring_chunks<CfgLarge>() + kSideChunks && kLargeRing 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef int int32x4_t __attribute__((ext_vector_type(4)));
 
-// Buffer resource of a raw byte buffer (base, wave-uniform, no stride, `bytes` in range: loads
+// Buffer resource of a raw byte buffer (base, no stride, `bytes` in range: loads
 // past it return zeros).
 FD_DEVICE int32x4_t buffer_rsrc(const void* base, uint32_t bytes = 0x7fffffffu) {
   const uint64_t p = reinterpret_cast<uint64_t>(base);
   int32x4_t r;
-  r.x = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(p)));
-  r.y = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(p >> 32) & 0xffffu));
+  r.x = static_cast<int>(static_cast<uint32_t>(p));
+  r.y = static_cast<int>(static_cast<uint32_t>(p >> 32) & 0xffffu);
   r.z = static_cast<int>(bytes);
   r.w = 0x00020000;
   return r;
 }
 
-// The resource in scalar registers that a load in inline assembly may read at once: the compiler
-// may have moved it there with vector instructions, and does not know that a vector memory
-// instruction must not follow those within five wait states.
-FD_DEVICE int32x4_t settled(int32x4_t r) {
-  asm volatile("s_nop 4" : "+s"(r));
-  return r;
-}
-
-// 16 bytes per lane from buffer offset voff + soff into LDS at lds_addr + 16 * lane
-// (lds_addr and soff wave-uniform).  Issued as inline assembly so that the compiler does
+// 16 bytes per lane from buffer offset `voff` into LDS at lds_addr + 16 * lane
+// (lds_addr wave-uniform).  Issued as inline assembly so that the compiler does
 // not wait for it before unrelated LDS reads; completion is awaited explicitly
 // with s_waitcnt vmcnt before the barrier that publishes a stage.
-FD_DEVICE void lds_dma16(uint32_t lds_addr, uint32_t voff, int32x4_t rsrc, uint32_t soff = 0) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+FD_DEVICE void lds_dma16(uint32_t lds_addr, uint32_t voff, int32x4_t rsrc) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :
-               : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff));
+               : "s"(lds_addr), "v"(voff), "s"(rsrc));
 }
 
 // Wait until at most N of this wave's vector-memory operations are in flight,
@@ -274,7 +266,7 @@ FD_DEVICE void row_operands(const fdh::GemmArgs& g, int M, int row0, int (&rtok)
   for (int i = 0; i < FM; ++i) {
     const int r = min(row0 + 32 * i, M - 1);
     rtok[i] = (KIND == fdh::GEMM_QKV || KIND == fdh::GEMM_EMBED) ? g.idx[r] : 0;
-    rreq[i] = (KIND == fdh::GEMM_RESID) ? fd::row_request(g.cu_q, g.n_req, r) : 0;
+    rreq[i] = (KIND == fdh::GEMM_RESID) ? fd::row_request(g.cu_q, g.n_req, g.row0 + r) : 0;
   }
 }
 
@@ -317,6 +309,8 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
   uint4* ring_mem = ring_all + group * (STAGES * Cfg::CHUNKS);
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
   const int l32 = lane & 31, lg = lane >> 5;
+  const int32x4_t rs_a = buffer_rsrc(g.act);
+  const int32x4_t rs_b = buffer_rsrc(g.wt);
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t ring_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)&ring_mem[0]));
 
@@ -350,34 +344,28 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
     t.nkt = ((t.split + 1) * nk) / S - t.kt0;
     return true;
   };
-  // The unit's first A and B rows as buffer bases (64 bits: the operands may be larger than the
-  // 2 GiB that an offset reaches), and the per-lane byte offsets from them (k = 0) of this lane's
-  // row and source chunk in each of its wave-loads.
-  const uint16_t *base_a, *base_b;
+  // per-lane byte offsets (k = 0) of this lane's row and source chunk in each of its wave-loads
   auto offsets = [&](const Unit& t, uint32_t (&o)[LOADS]) {
-    base_a = g.act + static_cast<size_t>(t.m0) * K;
-    base_b = g.wt + static_cast<size_t>(t.n0) * K;
 #pragma unroll
     for (int q = 0; q < LOADS; ++q) {
       const int blk = wave + WAVES * q;        // 8-row block in the concatenated A|B tile
       const int r = blk * RPW + lane / CPR;
       const int c = (lane % CPR) ^ Cfg::swz(r);
-      const int gr = (q < Cfg::LOADS_A) ? min(r, M - 1 - t.m0) : min(r - BM, N - 1 - t.n0);
-      o[q] = (static_cast<uint32_t>(gr) * static_cast<uint32_t>(K) + static_cast<uint32_t>(c * 8)) * 2;   // chunk = 8 bf16
+      const int gr = (q < Cfg::LOADS_A) ? min(t.m0 + r, M - 1) : min(t.n0 + (r - BM), N - 1);
+      o[q] = static_cast<uint32_t>((static_cast<size_t>(gr) * K + c * 8) * 2);   // chunk = 8 bf16
     }
   };
-  // the wave-loads of K-step kt of a unit (bases rs_a and rs_b, offsets o, first K-step kt0) into stage st
-  auto issue = [&](const int32x4_t& rs_a, const int32x4_t& rs_b, const uint32_t (&o)[LOADS], int kt0, int kt, int st) {
+  // the wave-loads of K-step kt of a unit (offsets o, first K-step kt0) into stage st
+  auto issue = [&](const uint32_t (&o)[LOADS], int kt0, int kt, int st) {
     const uint32_t buf = ring_base + static_cast<uint32_t>(st * Cfg::CHUNKS * 16);
     const uint32_t kb = static_cast<uint32_t>((kt0 + kt) * BK * 2);
 #pragma unroll
     for (int q = 0; q < LOADS; ++q)
-      lds_dma16(buf + static_cast<uint32_t>((wave_u + WAVES * q) * 64 * 16), o[q], q < Cfg::LOADS_A ? rs_a : rs_b, kb);
+      lds_dma16(buf + static_cast<uint32_t>((wave_u + WAVES * q) * 64 * 16), o[q] + kb, q < Cfg::LOADS_A ? rs_a : rs_b);
   };
   auto prologue = [&](const Unit& t, const uint32_t (&o)[LOADS]) {
-    const int32x4_t rs_a = settled(buffer_rsrc(base_a)), rs_b = settled(buffer_rsrc(base_b));
 #pragma unroll
-    for (int p = 0; p < STAGES - 1; ++p) issue(rs_a, rs_b, o, t.kt0, min(p, t.nkt - 1), p);
+    for (int p = 0; p < STAGES - 1; ++p) issue(o, t.kt0, min(p, t.nkt - 1), p);
   };
   // the bias of this lane's columns (split 0 only; the accumulators start there),
   // or, with overlap, zeros, and the tile's bias (wave 0) and row tokens (wave 1, QKV)
@@ -443,7 +431,6 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
         }
 
     const int nkt = cur.nkt, kt0 = cur.kt0;
-    const int32x4_t rs_a = settled(buffer_rsrc(base_a)), rs_b = settled(buffer_rsrc(base_b));   // kept for the K loop
     for (int it = 0; it < nkt; ++it) {
       // exactly STAGES - 2 younger stages (and, in the first step, the previous
       // unit's epilogue stores) are in flight: stage `it` has landed for every wave
@@ -453,7 +440,7 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
         wait_vm_barrier<(STAGES - 2) * LOADS>();
       // refill the slot every wave finished reading before this barrier (a repeat at the tail)
       const int kt_next = min(it + STAGES - 1, nkt - 1), st_next = (it + STAGES - 1) % STAGES;
-      issue(rs_a, rs_b, off, kt0, kt_next, st_next);
+      issue(off, kt0, kt_next, st_next);
       const uint4* sm = ring_mem + (it % STAGES) * Cfg::CHUNKS;
       bf16x8_t a[2][FM], b[2][FN];
       auto frag = [&](int ks, int slot) {
@@ -480,24 +467,21 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ks & 1][j], a[ks & 1][i], acc[i][j], 0, 0, 0);
       }
       // schedule: first fragments, then per k16 step one next-step read after each of the
-      // first FM + FN MFMAs, then the remaining MFMAs; with fewer MFMAs than reads (64-row by
-      // 32-column waves), every read after the first MFMA, so that they run beside the others
-      // (128x64 and 128x128 tiles of 512 threads: 1 to 3% less per product than one after each)
+      // first MFMAs, then what remains of either.  (Waves of 64 x 32 have two MFMAs to three reads;
+      // with all reads after the first MFMA a block alone, its weights in the caches, gains 2 to 3%
+      // per product, but a step, whose weights come from HBM, loses: 24 attention projections of
+      // the image step 541 us in pairs, 556.)
       __builtin_amdgcn_sched_group_barrier(0x100, FM + FN, 0);
 #pragma unroll
       for (int ks = 0; ks < BK / 16 - 1; ++ks) {
-        if constexpr (FM * FN < FM + FN) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, FM + FN, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - 1, 0);
-        } else {
+        constexpr int PAIRS = FM * FN < FM + FN ? FM * FN : FM + FN;
 #pragma unroll
-          for (int x = 0; x < FM + FN; ++x) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          }
-          if constexpr (FM * FN > FM + FN) __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - (FM + FN), 0);
+        for (int x = 0; x < PAIRS; ++x) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
+        if constexpr (FM + FN > PAIRS) __builtin_amdgcn_sched_group_barrier(0x100, FM + FN - PAIRS, 0);
+        if constexpr (FM * FN > PAIRS) __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - PAIRS, 0);
       }
       __builtin_amdgcn_sched_group_barrier(0x008, FM * FN, 0);
     }
@@ -565,7 +549,7 @@ FD_DEVICE void gemm_tiles(const fdh::GemmArgs& g, int slots, int M, uint4* ring_
 template <int KIND>
 __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(fdh::GemmArgs g, int slots) {
   __shared__ uint4 ring_mem[kSmallRing];
-  const int M = min(*g.m, g.n_max);
+  const int M = min(*g.m - g.row0, g.n_max);
   if (M <= 0) return;
   switch (fd::small_shape(M, g.N, g.K, slots, g.max_units)) {
     case 1: gemm_tiles<CfgWide, KIND>(g, slots, M, ring_mem); break;
@@ -577,7 +561,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(fdh::GemmA
 template <int KIND>
 __global__ __launch_bounds__(kLargeThreads, 2) void gemm_large_kernel(fdh::GemmArgs g, int cus) {
   __shared__ uint4 ring_mem[kLargeRing];
-  const int M = min(*g.m, g.n_max);
+  const int M = min(*g.m - g.row0, g.n_max);
   if (M <= 0) return;
   switch (fd::large_shape(M, g.N, g.K, cus, g.max_units)) {
     case fd::kLargeTile: gemm_tiles<CfgLarge, KIND>(g, cus, M, ring_mem); break;
@@ -597,7 +581,7 @@ __global__ __launch_bounds__(kLargeThreads, 2) void gemm_large_kernel(fdh::GemmA
 template <int KIND, class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS) void splitk_reduce_kernel(fdh::GemmArgs g, int slots) {
   constexpr int FM = Cfg::FM, FN = Cfg::FN, NB = FM * FN, THREADS = Cfg::THREADS;
-  const int M = min(*g.m, g.n_max);
+  const int M = min(*g.m - g.row0, g.n_max);
   if (M <= 0) return;
   const int tiles_m = (M + Cfg::BM - 1) / Cfg::BM, tiles_n = (g.N + Cfg::BN - 1) / Cfg::BN;
   const int tiles = tiles_m * tiles_n;
@@ -652,7 +636,7 @@ constexpr int kLoadsB = BN * kChunks / kThreads;
 
 __global__ __launch_bounds__(kThreads, 2) void embed_ragged_kernel(fdh::GemmArgs g) {
   __shared__ uint4 smem[2][(BM + BN) * kChunks];
-  const int M = min(*g.m, g.n_max);
+  const int M = min(*g.m - g.row0, g.n_max);
   const int N = g.N, K = g.K;
   const int tiles_m = (M + BM - 1) / BM;
   const int tiles_n = (N + BN - 1) / BN;
@@ -798,7 +782,8 @@ hipError_t launch_tiled(GemmKind kind, const GemmArgs& a, int max_units, bool la
 }
 }  // namespace
 
-hipError_t launch_gemm(GemmKind kind, const GemmArgs& a, hipStream_t s) {
+namespace {
+hipError_t launch_rows(GemmKind kind, const GemmArgs& a, hipStream_t s) {
   if (a.K % TBK == 0) {
     const bool large = fd::gemm_large(a.n_max, a.N, kind == GEMM_EMBED);
     const int max_units = a.partial && fd::gemm_may_split(a.n_max, a.N, large) ? a.max_units : 0;   // no scratch: never split
@@ -812,6 +797,28 @@ hipError_t launch_gemm(GemmKind kind, const GemmArgs& a, hipStream_t s) {
   const int grid = static_cast<int>(tiles < cap ? (tiles < 1 ? 1 : tiles) : cap);
   embed_ragged_kernel<<<grid, kThreads, 0, s>>>(a);
   return hipGetLastError();
+}
+}  // namespace
+
+// One launch, or several over as many rows each as the tile loads' offsets reach: 2 GiB of
+// activations.  (A 64-bit base per tile instead, with the K-step as a scalar offset, was faster on
+// warm weights but cost the products of a step, whose weights come from HBM, 2 to 7%.)
+hipError_t launch_gemm(GemmKind kind, const GemmArgs& a, hipStream_t s) {
+  if (static_cast<long long>(a.N) * a.K * 2 > kMaxGemmBytes) return hipErrorInvalidValue;   // the weights
+  const int cap = gemm_rows_per_launch(a.K);
+  for (int row0 = 0; row0 < a.n_max; row0 += cap) {
+    GemmArgs g = a;
+    const size_t r = static_cast<size_t>(row0);
+    g.row0 = row0;
+    g.n_max = a.n_max - row0 < cap ? a.n_max - row0 : cap;
+    g.act += r * a.K;
+    if (g.idx) g.idx += r;
+    if (g.out_bf16) g.out_bf16 += r * (kind == GEMM_QKV ? a.D : a.N);
+    if (g.out_f32) g.out_f32 += r * a.N;
+    const hipError_t e = launch_rows(kind, g, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace fdh

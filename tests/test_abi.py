@@ -115,6 +115,10 @@ def test_entry_points_validate_before_launch():
     for tokens, status in ((1 << 18, 3), ((1 << 18) - 1, 2)):
         long = fdl.FdPlan(tokens, 1, 1, tokens, tokens, *([0x1000] * 6))
         assert lib.fd_block_forward(ctypes.byref(long), ctypes.byref(d_wide), ctypes.byref(w), *small) == status
+    # an MLP of 2 GiB of weights, and one just below
+    for F, status in ((1 << 18, 3), ((1 << 18) - 64, 2)):
+        d_mlp = fdl.FdDims(64, 4096, 32, 128, F)
+        assert lib.fd_block_forward(ctypes.byref(plan), ctypes.byref(d_mlp), ctypes.byref(w), *small) == status
     # select: bad gate parameters, too many regions
     g = fdl.FdGate(-1.0, 0)
     assert lib.fd_select(ctypes.byref(plan), *([0x1000] * 2), g, *([0x1000] * 7), None) == 1
