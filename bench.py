@@ -215,9 +215,9 @@ def step_flops(w, M: int) -> float:
     return w.L * per_block + kernel_flops("embed", w, M) + kernel_flops("final", w, M)
 
 
-KERNEL_SOURCES = {"attn": ("k_attn.hip", "fd_common.h")}
+KERNEL_SOURCES = {"attn": ("k_attn.hip", "fd_attn_sched.h", "fd_rules.h", "fd_common.h")}
 for _g in ("gemm_qkv", "gemm_o", "gemm_mlp1", "gemm_mlp2"):
-    KERNEL_SOURCES[_g] = ("k_gemm.hip", "fd_common.h")
+    KERNEL_SOURCES[_g] = ("k_gemm.hip", "fd_gemm_rules.h", "fd_rules.h", "fd_common.h")
 
 
 def traffic_per_launch(kernel: str, workload: str):

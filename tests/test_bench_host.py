@@ -1,6 +1,8 @@
 """Host-side parts of bench.py (no GPU): the oracle baseline's fields on the tiny
-workload, its thread cap, and the refusal of more than one GPU."""
+workload, its thread cap, the sources a traffic figure depends on, and the refusal
+of more than one GPU."""
 import os
+import re
 import subprocess
 import sys
 
@@ -24,6 +26,20 @@ def test_cpu_baseline_fields_on_tiny(threads):
     assert r["host"]["nproc"] == os.cpu_count()
     assert isinstance(r["host"]["cpu"], str)
     assert "tiny step (M=128 active rows)" in r["sample"]
+
+
+def test_traffic_sources_name_every_header():
+    """A traffic figure is reported only while its kernel's code is unchanged, so the
+    sources watched hold every header of this library that the kernel's file includes."""
+    csrc = os.path.join(ROOT, "paper_2607_12121_amd", "csrc")
+
+    def includes(name):
+        with open(os.path.join(csrc, name), encoding="utf-8") as f:
+            found = [h for h in re.findall(r'#include "([^"]+)"', f.read()) if os.path.exists(os.path.join(csrc, h))]
+        return set(found).union(*(includes(h) for h in found))
+
+    for kernel, sources in bench.KERNEL_SOURCES.items():
+        assert set(sources[1:]) == includes(sources[0]), kernel
 
 
 def test_more_than_one_gpu_is_refused():
