@@ -5,7 +5,7 @@
 //
 // Work item = (head, query tile of one request).  Head dim 64 and 128: one
 // workgroup of 8 waves per CU (two per SIMD) works on 256 queries at a time, 32
-// per wave; head dim 16: 4 waves, two workgroups per CU.  Each wave computes
+// per wave; head dim 16: 4 waves, 128 queries.  Each wave computes
 // S^T = K Q^T (keys x queries), so a lane owns one query column: its running max
 // needs one half-wave exchange per tile and its running sum none until the end;
 // S^T feeds O^T = V^T P^T directly as the B operand.  Every head dim runs a
@@ -106,7 +106,7 @@ struct ACfg {
   // Waves per workgroup.  Head dim 64 and 128: eight (two per SIMD) in one workgroup
   // per CU, so every K/V tile brought into LDS serves 256 queries (half the LDS
   // writes per query of two four-wave workgroups; video attention -8%, image -9%);
-  // head dim 16: four, two workgroups per CU.
+  // head dim 16: four.
   static constexpr int WAVES = DH >= 64 ? 8 : 4;
   static constexpr int THREADS = WAVES * 64;
   static constexpr int QB = WAVES * QG * 32;            // queries per unit
@@ -115,7 +115,7 @@ struct ACfg {
   static constexpr int STAGE = 2 * TILE;                // K tile then V tile
   // Software pipeline: S of tile t + 1 next to the softmax of tile t.  Head dim <= 64:
   // a ring of four K|V stages.  Head dim 128: K and V in two-slot rings of their own
-  // (K two tiles ahead, V one), 64 KB, so that two workgroups share a CU.
+  // (K two tiles ahead, V one), 64 KB.
   static constexpr bool PIPE = true;
   static constexpr bool SPLIT = DH >= 128;
   static constexpr int AHEAD = DH >= 128 ? 2 : 3;        // operand reads ahead of their MFMAs (head dim 128: registers)
@@ -124,7 +124,7 @@ struct ACfg {
   static constexpr int LOADS = STAGE / 64 / WAVES;      // 1 KB wave-loads per wave per stage
   static constexpr int KS = DH / 16;                    // k16 steps of S^T over d
   static constexpr int DT = (DH + 31) / 32;             // 32-row tiles of O^T
-  static constexpr int OCC = 8 / WAVES;                 // workgroups per CU
+  static constexpr int OCC = 8 / WAVES;                 // workgroups per CU that the registers leave room for
   static constexpr int WPE = WAVES * OCC / 4;           // waves per SIMD
   static_assert(THREADS <= kMaxThreads, "partial slots sized for kMaxThreads");
   static_assert(STAGE % (64 * WAVES) == 0, "stage must split into whole wave-loads");
@@ -595,8 +595,9 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
         // three stages that overlap across pairs: exponents of pair pp, scaled scores
         // of pair pp + 1, bf16 pack and row sum of pair pp - 1, so no instruction waits
         // for the one before it; a job follows each pair.  The order is pinned per pair.
-        // (Packed batch, same card: 290 us with each pair's four steps in turn and reads two
-        // jobs ahead, 284 so and three ahead; image 73.6 / 72.0, video block 2424 / 2401.)
+        // (Pass and merge, us, each pair's four steps in turn and reads two jobs ahead / so and
+        // three ahead, one card: packed batch 268 / 263, image 70.0 / 68.6, audio 26.3 / 25.6,
+        // video 1764 / 1741.)
         float lsum[QG][4];   // four independent chains of row-sum dot products
 #pragma unroll
         for (int g = 0; g < QG; ++g)
@@ -894,9 +895,10 @@ hipError_t launch_attention(const uint16_t* q, const uint16_t* kc, const uint16_
   if (B < 1 || B > kMaxAttnRequests) return hipErrorInvalidValue;   // the schedule tables' size
   const int occ = dh >= 128 ? ACfg<128>::OCC : ACfg<64>::OCC;
   const int slots = occ * num_cus();
-  // persistent grid: the resident slots, fewer when even one key tile per share
-  // would leave some idle (upper bound on the items: every request adds at most
-  // one partial query tile)
+  // persistent grid: a workgroup per CU, fewer when even one key tile per share
+  // would leave some idle (upper bound on the items of 256 queries: every request adds
+  // at most one partial query tile).  Head dim 16 takes the grid of head dim 64: its
+  // items, of 128 queries, may be twice as many, and each share walks what it gets.
   const int qb = dh >= 128 ? ACfg<128>::QB : ACfg<64>::QB;
   const long long items = static_cast<long long>((n_max + qb - 1) / qb + B) * H;
   const int nkv_max = (max_req_tokens + KB - 1) / KB;

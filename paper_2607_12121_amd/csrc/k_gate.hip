@@ -166,8 +166,8 @@ FD_DEVICE int compact_chunk(int u0, int N, const int32_t* __restrict__ token_reg
 // Patch Gate in one workgroup (R <= 4096, B <= 1024): decisions, skip counters, cu_q
 // and m; with COMPACT also the index list, chunk by chunk.  Bound by latency: every
 // global load of a thread's regions is issued before the first barrier, the sums and
-// decisions then run from registers and LDS (4.5 us at 140 regions, 8.3 at 4096 without
-// the list).
+// decisions then run from registers and LDS (4.5 us at 140 regions, 9.1 at 4096 without
+// the list; inside a step 5.7 at 140).
 template <bool COMPACT>
 __global__ __launch_bounds__(kSelThreads) void gate_select_kernel(
     int R, int B, int N, const int32_t* __restrict__ region_req, const int32_t* __restrict__ req_reg_off,
@@ -272,9 +272,12 @@ __global__ __launch_bounds__(kSelThreads) void gate_select_kernel(
 // The index list of a larger batch, one workgroup per chunk of tokens, from the mask
 // and cu_q that gate_select_kernel<false> left (the kernel boundary orders them): the
 // active tokens before the chunk are those of the earlier requests (cu_q) and those
-// of the chunk's first request before it, which the workgroup counts.  Compacting in the
-// one workgroup above, each thread walking its own run of tokens, took the select to 49 us
-// at 32760 tokens and 338 at 262144; now 4.5 + 5.8 and 8.3 + 4.2 us.
+// of the chunk's first request before it, which the workgroup counts: of one long request
+// the last workgroup counts nearly all, through two dependent loads a token, and that is
+// what the kernel's time is (8 requests of 4096 tokens 4.2 us, one of 32760 6.1, where the
+// tables come from HBM inside a step 11.1).  Compacting in the one workgroup above, each
+// thread walking its own run of tokens, took the select to 53 us at 32760 tokens of one
+// request and 359 at 262144 of 64; both launches together, replayed: 10.5 and 12.8 us.
 __global__ __launch_bounds__(kSelThreads) void gate_compact_kernel(int N, const int32_t* __restrict__ token_region,
                                                                    const int32_t* __restrict__ region_req,
                                                                    const int32_t* __restrict__ req_tok_off,

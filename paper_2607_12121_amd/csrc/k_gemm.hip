@@ -13,15 +13,17 @@
 // 512-thread workgroups, one per CU, with 256x256 (half the LDS traffic per flop, which
 // bounds the K loop: at 256x256 about 2560 LDS clocks beside 2048 MFMA clocks per K-step),
 // 192x256, 128x256, 128x128 or pairs of 128x64 tiles.  With one shape for long batches
-// (256x256) and the small kernel up to 16384 tokens, the audio block's dense warm-up of
-// 13600 rows took 695 us (now 612), the image block at 2048 of 40960 rows 453 (328).
+// (256x256) and the small kernel up to 16384 tokens, the four products of an audio block's
+// dense warm-up (14280 rows) took 514 us (now 417), of an image block at 1920 of 40960 rows
+// 292 (176).
 // Tiles stream from HBM straight into LDS (buffer_load ... lds, 16
 // bytes per lane) through a ring of stages with one barrier per K-step; every
 // stage is issued (the last one re-issued at the tail) so the wait count is a
 // constant.  In LDS each tile row is eight 16-byte chunks, chunk c of row r at
 // c ^ ((r >> 1) & 7): the 16 lanes that read one MFMA fragment together hit 16
 // different 16-byte bank groups.  Inside a K-step the next k16 fragments are read
-// while the current MFMAs run (one read after each of the first MFMAs).  Rows
+// while the current MFMAs run (one read after each of the first MFMAs).  The loads'
+// offsets stay below 2 GiB; longer activations run as several launches.  Rows
 // past M (or N) re-read the last valid row; their results are never stored.
 //
 // Split-K (128x128 tiles, when the tile count leaves CUs idle and K is long):

@@ -63,7 +63,7 @@ def test_index_list_at_chunk_edges(sizes, regions, frac):
 
 @pytest.mark.parametrize("C,size", [(16, 1), (64, 16), (64, 17), (64, 1024), (64, 1025), (256, 256), (256, 257), (48, 1365)])
 def test_score_one_pass_and_cut(C, size):
-    """Regions of up to 65536 values in one pass (narrow and wide workgroups), larger ones cut."""
+    """Regions of two requests around the sizes at which the workgroup widens and a region is cut."""
     rng = np.random.default_rng([C, size])
     lay = _layout(rng, [3 * size, size + 1], 2)
     N, R = len(lay.token_region), lay.n_regions

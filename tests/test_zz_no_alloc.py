@@ -1,8 +1,9 @@
 """The entry point that allocates nothing, fd_region_score_noalloc (built-in
 scratch for the partial sums), against fd_region_score (caller workspace),
 through the C ABI: bit-identical scores, and within 1e-12 of the oracle, on two
-calls in a row, the second on a smaller input; an input whose partials exceed
-the built-in scratch is rejected before anything is enqueued."""
+calls in a row, the second on a smaller input (both in one pass, without partials:
+inputs that use the scratch are compared with the gate's edge cases); an input
+whose partials exceed the built-in scratch is rejected before anything is enqueued."""
 import ctypes
 
 import numpy as np
@@ -43,8 +44,8 @@ def _both(name: str, step: int):
 
 
 def test_noalloc_score_equals_workspace_score_on_two_calls():
-    # first the video request (140 regions x 8 chunks of partials), then a smaller
-    # input (the image request: 64 regions x 2 chunks) on the same built-in scratch
+    # first the video request (140 regions of 14976 values), then a smaller input (the
+    # image request: 64 regions of 4096)
     for name, step in (("video", 0), ("image", 1)):
         ref, got, want = _both(name, step)
         assert np.array_equal(got, ref), f"{name}: no-alloc scores differ from the workspace entry point"
