@@ -165,15 +165,15 @@ struct AttnSched {
     locate(q, i_start, nkv, head, b, first, tau);
     return i_start == q ? q : i_start + nkv;
   }
-  // first and last share of the cut item [i_start, i_end) that share w holds a piece of: w or a
-  // neighbour, mostly (finding them by a division per end measured slower)
-  FD_RULE void pieces_of(int w, long long i_start, long long i_end, int& f, int& l) const {
-    f = l = w;
-    while (bound(f) > i_start) --f;
-    while (bound(l + 1) < i_end) ++l;
+  // Scratch slot of share w's piece of key tiles [kt0, kt1) of an item of nkv: -1 for a whole item.
+  FD_RULE static int slot_of(int w, int kt0, int kt1, int nkv) { return kt0 > 0 ? 2 * w : kt1 < nkv ? 2 * w + 1 : -1; }
+  // slot of piece j of a cut item whose first piece is in share x
+  FD_RULE static int slot_at(int x, int j) { return 2 * (x + j) + (j == 0); }
+  // last share that holds a piece of the item that ends at tile-step i_end and goes on past share x
+  FD_RULE int last_share(int x, long long i_end) const {
+    while (bound(x + 1) < i_end) ++x;
+    return x;
   }
-  // scratch slot of piece j of a cut item whose first piece is in share f
-  FD_RULE static int slot_of(int f, int j) { return j == 0 ? 2 * f + 1 : 2 * (f + j); }
 };
 
 }  // namespace fd

@@ -290,11 +290,10 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
   }
 
   // One piece of work: key tiles [kt0, kt1) of query tile tau (of request b, whose
-  // first query tile is number `first`) under head `head`; piece `piece` of the
-  // `npieces` that cover this (head, tile) item in key order, the first of them in
-  // share `share0`.
+  // first query tile is number `first`) under head `head`; a piece of a cut item goes
+  // to scratch slot `slot_no`, a whole item (-1) to the outputs.
   auto run_piece = [&](const int head, const int tau, const int b, const int first, const int kt0, const int kt1,
-                       const int piece, const int npieces, const int share0) {
+                       const int slot_no) {
     const int q_lo = cu_q[b] + (tau - first) * QB;
     const int q_hi = cu_q[b + 1];
     const int k_beg = req_tok_off[b], k_end = req_tok_off[b + 1];
@@ -337,32 +336,35 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
       dma_off[q] = static_cast<uint32_t>(r) * static_cast<uint32_t>(2 * D) + static_cast<uint32_t>(c * 16);
     }
     // wave-loads q in [Q0, Q1) of key tile kt (global index): K blocks to kbuf, V
-    // blocks to vbuf, 1 KB per block
+    // blocks to vbuf, 1 KB per block.  The clamped offsets of a ragged last tile are formed
+    // beside one set of loads, at head dim 64 out of the loop's way (packed batch 285 us with
+    // two sets, 280 so); head dim 128 takes 1 to 2% more either of the other ways, and head
+    // dim 16, whose loop is short, 4% more with one set.
     auto issue_q = [&](int kt, uint32_t kbuf, uint32_t vbuf, auto q0_tag, auto q1_tag) {
       constexpr int Q0 = decltype(q0_tag)::value, Q1 = decltype(q1_tag)::value;
       const uint32_t soff = static_cast<uint32_t>(fd::uniform(kt - kt0)) * static_cast<uint32_t>(KB * 2) * static_cast<uint32_t>(D);
-      if (kt < n_full) {
-#pragma unroll
-        for (int q = Q0; q < Q1; ++q) {
-          const int blk = wave_u + C::WAVES * q;            // wave-uniform
-          const bool is_v = loads_v(q, blk);
-          const uint32_t dst = is_v ? vbuf + static_cast<uint32_t>((blk - TILE_BLKS) * 64 * 16)
-                                    : kbuf + static_cast<uint32_t>(blk * 64 * 16);
-          lds_dma16(dst, dma_off[q], is_v ? rs_v : rs_k, soff);
-        }
-      } else {
-        const int last = k_end - 1 - (k_beg + kt * KB);
-#pragma unroll
-        for (int q = Q0; q < Q1; ++q) {
-          const int blk = wave_u + C::WAVES * q;            // wave-uniform
-          const bool is_v = loads_v(q, blk);
-          const int r = (blk - (is_v ? TILE_BLKS : 0)) * RPL + lane / KCH;
+      auto load = [&](int q, auto clamp) {   // clamped offsets: -1 where the tile needs them
+        const int blk = wave_u + C::WAVES * q;            // wave-uniform
+        const bool is_v = loads_v(q, blk);
+        uint32_t off = dma_off[q];
+        if (clamp.value >= 0 ? clamp.value : DH == 64 ? __builtin_expect(kt >= n_full, 0) : kt >= n_full) {
+          const int r = (blk - (is_v ? TILE_BLKS : 0)) * RPL + lane / KCH, last = k_end - 1 - (k_beg + kt * KB);
           const int c = (lane % KCH) ^ (is_v ? C::fv(r) : C::fk(r));
-          const uint32_t off = static_cast<uint32_t>(min(r, last)) * static_cast<uint32_t>(2 * D) + static_cast<uint32_t>(c * 16);
-          const uint32_t dst = is_v ? vbuf + static_cast<uint32_t>((blk - TILE_BLKS) * 64 * 16)
-                                    : kbuf + static_cast<uint32_t>(blk * 64 * 16);
-          lds_dma16(dst, off, is_v ? rs_v : rs_k, soff);
+          off = static_cast<uint32_t>(min(r, last)) * static_cast<uint32_t>(2 * D) + static_cast<uint32_t>(c * 16);
         }
+        const uint32_t dst = is_v ? vbuf + static_cast<uint32_t>((blk - TILE_BLKS) * 64 * 16)
+                                  : kbuf + static_cast<uint32_t>(blk * 64 * 16);
+        lds_dma16(dst, off, is_v ? rs_v : rs_k, soff);
+      };
+      if constexpr (DH >= 64) {
+#pragma unroll
+        for (int q = Q0; q < Q1; ++q) load(q, std::integral_constant<int, -1>{});
+      } else if (kt < n_full) {
+#pragma unroll
+        for (int q = Q0; q < Q1; ++q) load(q, std::integral_constant<int, 0>{});
+      } else {
+#pragma unroll
+        for (int q = Q0; q < Q1; ++q) load(q, std::integral_constant<int, 1>{});
       }
     };
     using IQ0 = std::integral_constant<int, 0>;
@@ -708,14 +710,14 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
 #pragma unroll
     for (int g = 0; g < QG; ++g) l_run[g] = half_sum(l_run[g]);
 
-    if (CUT && npieces > 1) {
+    if (CUT && slot_no >= 0) {
       // a piece of a cut item: O / sum and, for attn_combine_kernel, (max, sum) in fp32,
       // lane-major (quad q of thread t at word q * THREADS + t, then, past the slot's O
       // area, the (max, sum) pair of group g at float2 g * THREADS + t).  The quads are
       // fp32; where many pieces make their traffic count (head dim <= 64, work for the
       // whole grid: image 3 us) bf16, which a convex combination of V rows never leaves.
       constexpr int E = QG * (DT * 16 + 2);
-      float* slot = partial + static_cast<size_t>(Sched::slot_of(share0, piece)) * (E * C::THREADS);
+      float* slot = partial + static_cast<size_t>(slot_no) * (E * C::THREADS);
       uint2* quads = reinterpret_cast<uint2*>(slot) + tid;
       fd::f32x2_t* ml = reinterpret_cast<fd::f32x2_t*>(slot + QG * DT * 16 * C::THREADS) + tid;
 #pragma unroll
@@ -753,15 +755,13 @@ __global__ __launch_bounds__(ACfg<DH>::THREADS) __attribute__((amdgpu_waves_per_
     sch.locate(p, i_start, nkv, head, b, first, tau);
     if (b >= B) break;   // unreachable: p < work
     if constexpr (!CUT) {
-      run_piece(head, tau, b, first, 0, nkv, 0, 1, w);
+      run_piece(head, tau, b, first, 0, nkv, -1);
       p += nkv;
     } else {
       const long long i_end = i_start + nkv;
       const int kt0 = static_cast<int>(p - i_start);
       const int kt1 = static_cast<int>((p_end < i_end ? p_end : i_end) - i_start);
-      int f = w, l = w;
-      if (sch.cut) sch.pieces_of(w, i_start, i_end, f, l);
-      run_piece(head, tau, b, first, kt0, kt1, w - f, l - f + 1, f);
+      run_piece(head, tau, b, first, kt0, kt1, Sched::slot_of(w, kt0, kt1, nkv));
       p = i_start + kt1;
     }
   }
@@ -789,12 +789,10 @@ FD_DEVICE void combine_items(uint16_t* __restrict__ O, int D, int H, const int32
   int nkv, head, b, first, tau;
   sch.locate(p_end - 1, i_start, nkv, head, b, first, tau);
   if (b >= B || i_start < p0 || i_start + nkv <= p_end) return;
-  int f, l;
-  sch.pieces_of(x, i_start, i_start + nkv, f, l);
-  const int npieces = l - x + 1;
+  const int npieces = sch.last_share(x, i_start + nkv) - x + 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lg = lane >> 5;
   const int q_lo = cu_q[b] + (tau - first) * QB, q_hi = cu_q[b + 1];
-  auto slot = [&](int j) { return partial + static_cast<size_t>(Sched::slot_of(x, j)) * (E * C::THREADS); };
+  auto slot = [&](int j) { return partial + static_cast<size_t>(Sched::slot_at(x, j)) * (E * C::THREADS); };
   auto ml_of = [&](int j, int g) {
     return reinterpret_cast<const fd::f32x2_t*>(slot(j) + QG * DT * 16 * C::THREADS)[g * C::THREADS + tid];
   };

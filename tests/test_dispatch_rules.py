@@ -16,8 +16,9 @@ SHIM = r"""
 #include "fd_attn_sched.h"
 #include "fd_gemm_rules.h"
 namespace {
-// Every piece of every share as attn_fwd_kernel walks them, eight numbers each: share, head,
-// query tile, request, first and last + 1 key tile, number in its item, pieces of its item.
+// Every piece of every share as attn_fwd_kernel walks them, eight numbers each: share, head, query
+// tile, request, first and last + 1 key tile, scratch slot, and for a first piece, from which the
+// merge starts, the item's last share.
 template <int QB, int DH, bool TABLES, bool CUT>
 int pieces(const int32_t* cu_q, const int32_t* tok, int B, int H, int G, int nkv_max, int* out, int cap, int* cut) {
   static fd::SchedTables t;
@@ -41,10 +42,9 @@ int pieces(const int32_t* cu_q, const int32_t* tok, int B, int H, int G, int nkv
       int nkv, head, b, first, tau;
       s.locate(p, i0, nkv, head, b, first, tau);
       const long long i1 = i0 + nkv, e = p_end < i1 ? p_end : i1;
-      int f = w, l = w;
-      if (s.cut) s.pieces_of(w, i0, i1, f, l);
       if (n == cap) return -1;
-      const int row[8] = {w, head, tau, b, static_cast<int>(p - i0), static_cast<int>(e - i0), w - f, l - f + 1};
+      const int k0 = static_cast<int>(p - i0), k1 = static_cast<int>(e - i0);
+      const int row[8] = {w, head, tau, b, k0, k1, s.slot_of(w, k0, k1, nkv), k0 == 0 && k1 < nkv ? s.last_share(w, i1) : -1};
       for (int k = 0; k < 8; ++k) out[8 * n + k] = row[k];
       ++n;
       p = e;
@@ -70,6 +70,7 @@ int gemm_splits(int n_max, int M, int N, int K, int cus) {
 int attn_may_cut(int dh, int heads, int requests, long long tokens, int max_request_tokens, int G) {
   return fd::attn_may_cut(dh, heads, requests, tokens, max_request_tokens, 256, G);
 }
+int attn_slot_at(int x, int j) { return fd::AttnSched<256, 64, true, true>::slot_at(x, j); }
 long long div_steps(long long q, long long d) { return fd::div_steps(q, d); }
 int attn_pieces(int dh, int tables, int may_cut, const int32_t* cu_q, const int32_t* tok, int B, int H, int G, int nkv_max,
                 int* out, int cap, int* cut) {
@@ -210,8 +211,9 @@ def test_attention_schedule_beyond_32_bits(rules):
 @pytest.mark.parametrize("dh", [16, 64, 128])
 def test_attention_schedule_covers_every_tile_step_once(rules, seed, dh):
     """Random batches (requests without active rows, ragged ends, one token): whole and cut, walked
-    and from tables, every (head, query tile) runs over all its key tiles exactly once, its pieces
-    numbered in key order, each in a scratch slot of its own, and whole where nothing may be cut."""
+    and from tables, every (head, query tile) runs over all its key tiles exactly once, its pieces in
+    key order in consecutive shares, each in a scratch slot of its own where the merge, which starts
+    from the first, looks for it, and whole where nothing may be cut."""
     rng = np.random.default_rng([seed, dh])
     B = int(rng.choice([1, 2, 3, 17, 40]))
     H = int(rng.choice([1, 2, 12, 16]))
@@ -233,21 +235,25 @@ def test_attention_schedule_covers_every_tile_step_once(rules, seed, dh):
                                   int(nk.max()), out.ctypes.data_as(ctypes.c_void_p), cap, ctypes.byref(cut))
             assert 0 <= k <= cap
             items, slots = {}, set()
-            for w, h, t, b, k0, k1, j, np_ in out[:k].tolist():
+            for w, h, t, b, k0, k1, slot, last in out[:k].tolist():
                 assert 0 <= w < G and 0 <= k0 < k1
-                items.setdefault((h, t, b), []).append((j, k0, k1, np_, w))
-                if np_ > 1:
-                    slot = 2 * (w - j) + 1 if j == 0 else 2 * w
-                    assert 0 <= slot < 2 * G and slot not in slots
+                items.setdefault((h, t, b), []).append((k0, k1, w, slot, last))
+                assert slot not in slots
+                if slot >= 0:
+                    assert slot < 2 * G
                     slots.add(slot)
             assert set(items) == set(want)
             for key, ps in items.items():
                 ps.sort()
-                assert [p[0] for p in ps] == list(range(len(ps))) and all(p[3] == len(ps) for p in ps)
-                assert [p[4] for p in ps] == list(range(ps[0][4], ps[0][4] + len(ps)))
-                assert ps[0][1] == 0 and ps[-1][2] == want[key]
-                assert all(a[2] == b_[1] for a, b_ in zip(ps, ps[1:]))
-                assert may_cut or len(ps) == 1
+                x = ps[0][2]
+                assert [p[2] for p in ps] == list(range(x, x + len(ps)))
+                assert ps[0][0] == 0 and ps[-1][1] == want[key]
+                assert all(a[1] == b_[0] for a, b_ in zip(ps, ps[1:]))
+                if len(ps) == 1:
+                    assert ps[0][3:] == (-1, -1)
+                else:
+                    assert may_cut and ps[0][4] == ps[-1][2]
+                    assert [p[3] for p in ps] == [rules.attn_slot_at(x, j) for j in range(len(ps))]
             work = H * int((nt * nk).sum())
             if cut.value and work >= 4 * G:   # all shares used: share w holds [floor(w work / G), floor((w + 1) work / G))
                 steps = np.zeros(G, np.int64)
