@@ -77,7 +77,7 @@ struct AttnSched {
   int tiles;              // query tiles over all requests
   long long work_head;    // tile-steps of one head (key tiles summed over every query tile)
   long long work;         // ... of every head
-  long long per;          // work = per * G + extra
+  long long per;          // work = per * G + extra; little work: shares of per, those past the work empty
   int extra;
   uint32_t inv;           // 2^32 / G, rounded up: x / G = (x * inv) >> 32 for 0 <= x <= G * G, 8 <= G <= 1024
   bool cut;
@@ -96,23 +96,21 @@ struct AttnSched {
       }
     }
     work = work_head * H;
-    split();
+    per = div_steps(work, G);
+    extra = static_cast<int>(work - per * G);
+    inv = 0xffffffffu / static_cast<uint32_t>(G) + 1;
     if constexpr (CUT) {
       narrow = work >= G;
       cut = G % kXcds == 0 && attn_cuts(DH, tiles * H, H, work_head, tiles, per + (extra > 0), nkv_max, G, 0);
       if (cut) {   // little work on as many workgroups as give each kMinShareSteps tile-steps
         const long long up = ((work + kMinShareSteps - 1) / kMinShareSteps + kXcds - 1) / kXcds * kXcds;
-        if (up < G) {
+        if (up < G) {   // whole: items of a multiple of it are cut at share bounds only
           G = static_cast<int>(up);
-          split();
+          per = kMinShareSteps;
+          extra = 0;
         }
       }
     }
-  }
-  FD_RULE void split() {
-    per = div_steps(work, G);
-    extra = static_cast<int>(work - per * G);
-    inv = 0xffffffffu / static_cast<uint32_t>(G) + 1;
   }
   // the share run by workgroup `blk` (G: none)
   FD_RULE int share(int blk) const {
@@ -159,7 +157,8 @@ struct AttnSched {
     if (x >= G) return work;
     // floor(x * work / G)
     const long long q = x * per + static_cast<long long>((static_cast<uint64_t>(static_cast<uint32_t>(x) * extra) * inv) >> 32);
-    if (cut || q >= work) return q;
+    if (q >= work) return work;
+    if (cut) return q;
     long long i_start;
     int nkv, head, b, first, tau;
     locate(q, i_start, nkv, head, b, first, tau);

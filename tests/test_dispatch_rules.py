@@ -259,6 +259,10 @@ def test_attention_schedule_covers_every_tile_step_once(rules, seed, dh):
                 steps = np.zeros(G, np.int64)
                 np.add.at(steps, out[:k, 0], out[:k, 5] - out[:k, 4])
                 np.testing.assert_array_equal(steps, np.diff([w * work // G for w in range(G + 1)]))
+            elif cut.value and work <= 4 * (G - 8):   # little work: shares of four tile-steps
+                steps = np.zeros(G, np.int64)
+                np.add.at(steps, out[:k, 0], out[:k, 5] - out[:k, 4])
+                np.testing.assert_array_equal(steps, np.diff([min(4 * w, work) for w in range(G + 1)]))
             seen.append((tables, may_cut, cut.value, sorted(out[:k].tolist())))
     # the walked and the tabled schedule are the same
     assert [s[1:] for s in seen if s[0] == 0] == [s[1:] for s in seen if s[0] == 1]
