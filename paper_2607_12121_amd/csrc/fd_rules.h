@@ -47,7 +47,8 @@ FD_RULE bool attn_cuts(int dh, int items, int heads, long long work_head, int ti
     // the longest item: every query tile has a tile-step, so one has no more than the rest leaves
     const long long longest = nkv_max < work_head - tiles + 1 ? nkv_max : work_head - tiles + 1;
     const long long gain = longest - (part > kMinShareSteps ? part : kMinShareSteps) - margin;
-    return dh >= 128 ? 8 * gain > 40 + items : 40 * gain > 160 + items;
+    // items that are two shares each have no piece beyond those: 128 of 24 50 / 50 us, of 32 63 / 58
+    return dh >= 128 ? 8 * gain > (2 * items == G ? 112 : 40 + items) : 40 * gain > 160 + items;
   }
   // Items of one length run in whole rounds; of a mixed batch the longest share is somewhere
   // between its part and one longest item more.

@@ -147,6 +147,15 @@ def test_attention_cut_head_dim_128(rules, batch, cut):
 
 
 @pytest.mark.parametrize("batch,cut", [
+    ([(8, 307, 1024)], False), ([(8, 307, 1536)], False), ([(2, 2048, 2048)], True), ([(8, 410, 2048)], True),
+    ([(8, 200, 2048)], True),
+])
+def test_attention_cut_two_shares_per_item(rules, batch, cut):
+    """8 heads of 128, 128 items on 256 workgroups (64 in the last): cut from 32 key tiles on."""
+    assert _cuts(rules, 128, 8, batch) == cut
+
+
+@pytest.mark.parametrize("batch,cut", [
     ([(28, 77, 512)], False), ([(16, 1024, 1024)], False), ([(28, 512, 512)], False), ([(8, 1024, 1024)], False),
     ([(2, 1536, 1536)], False), ([(4, 614, 2048)], False), ([(1, 16384, 16384)], False),
     ([(1, 51, 1024)], True), ([(1, 1024, 2048)], True), ([(8, 205, 4096)], True), ([(2, 3072, 3072)], True),
